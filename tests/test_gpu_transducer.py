@@ -96,3 +96,46 @@ def test_constant_logprobs_and_invalid_lengths():
     with pytest.raises(tbs.TbsError):
         tbs.transducer_forward("standard", torch.zeros((1, 2, 1025), device="cuda"),
                                torch.zeros((1, 2, 1024), device="cuda"), [[2, 3]])
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("B,T,U", [
+    (3, 1, 0), (3, 1, 7), (2, 16, 126), (2, 17, 127), (2, 33, 128),  # chunk and lane edges
+    (2, 90, 255), (2, 90, 256), (300, 20, 30), (260, 12, 200), (1, 3, 1023),
+])
+def test_ring_shapes(kind, B, T, U):
+    """Sizes at the edges of the kernels' splits: cells per lane (64, 128, 256, ...), rows
+    per chunk, more utterances than compute units, and eq. (1)'s widest rings."""
+    blank, label, frames, labels = _inputs(B + T + U, B, T, U)
+    if kind != "standard":
+        labels = np.minimum(labels, frames)
+    _check(kind, blank, label, frames, labels)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_extreme_log_probabilities(kind):
+    """Values on both sides of what the linear domain takes: steep ones of -299, and
+    utterances with -inf, -1e30 or 1e3 among ordinary ones.  A NaN in a cell that is not
+    read changes nothing, and one that is read stays within its utterance."""
+    import torch
+    from paper_2211_00484_amd import tbs
+    blank, label, frames, labels = _inputs(5, 8, 60, 20, ragged=False)
+    blank[0] -= 290.0
+    label[1] = -299.0
+    label[2, :, 3] = -np.inf
+    blank[3, 7, 2] = -1e30
+    label[4, 5, 5] = 1e3
+    blank[5, :, 1:] = -np.inf
+    _check(kind, blank, label, frames, labels)
+    frames[6], labels[6] = 50, 15
+    blank[6, 51:], blank[6, :, 17:], label[6, 51:], label[6, :, 17:] = (np.nan,) * 4
+    blank[7, 30, 2] = np.nan
+    total, _, status = tbs.transducer_forward(kind, torch.from_numpy(blank).cuda(),
+                                              torch.from_numpy(label).cuda(),
+                                              np.stack([frames, labels], 1))
+    want, _ = oracle.transducer_forward(kind, blank[:7], label[:7], frames[:7], labels[:7])
+    total = total.cpu().numpy()
+    assert (status.cpu().numpy() == 0).all()
+    fin = np.isfinite(want)
+    assert np.array_equal(total[:7][~fin], want[~fin])
+    assert np.allclose(total[:7][fin], want[fin], rtol=1e-9, atol=1e-9)
