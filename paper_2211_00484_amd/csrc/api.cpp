@@ -176,9 +176,12 @@ struct tbs_model {
   int dev = 0, ncu = 0, coop = 0;   // device, compute units, cooperative launch support
   XBuf xbuf;
   unsigned spin_limit = kDefaultSpinLimit;  // polls before a grouped-kernel wait gives up
+  std::vector<char*> tables;  // allocations of the tables below
   float* P0 = nullptr;
   float* P1 = nullptr;
-  float* Wf = nullptr;
+  uint16_t* Ws = nullptr;
+  uint16_t* Wsi = nullptr;
+  float* zscale = nullptr;
   uint16_t* Wb = nullptr;
   void* Wi = nullptr;
   float* bias = nullptr;
@@ -227,7 +230,9 @@ ModelDev model_dev(const tbs_model* m) {
   d.bf16 = m->bf16;
   d.P0 = m->P0;
   d.P1 = m->P1;
-  d.Wf = m->Wf;
+  d.Ws = m->Ws;
+  d.Wsi = m->Wsi;
+  d.zscale = m->zscale;
   d.Wb = m->Wb;
   d.Wi = m->Wi;
   d.bias = m->bias;
@@ -804,14 +809,43 @@ tbs_status tbs_model_create(int32_t vocab_size, int32_t dim, int32_t context_siz
   if (e == hipSuccess)
     e = hipDeviceGetAttribute(&m->coop, hipDeviceAttributeCooperativeLaunch, m->dev);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&m->busy, hipEventDisableTiming);
-  if (e == hipSuccess) e = dalloc(&m->P0, VK);
-  if (e == hipSuccess) e = dalloc(&m->P1, VK);
-  if (e == hipSuccess) e = m->bf16 ? dalloc(&m->Wb, VpK) : dalloc(&m->Wf, VpK);
-  if (e == hipSuccess) e = dalloc((char**)&m->Wi, VpK * (m->bf16 ? 2 : 4));
-  if (e == hipSuccess) e = dalloc(&m->bias, (size_t)m->V);
+  // The tables: one allocation when any of them is large (a hipMalloc of 2 MiB or more
+  // takes some 25 us, a smaller one about 1 us), else one each.
+  {
+    const size_t wb = m->bf16 ? 2 : 4;  // bytes per packed weight (an fp16 pair: 4)
+    const size_t sizes[7] = {VK * 4, VK * 4, VpK * wb, m->bf16 ? 0 : VpK * wb, VpK * wb,
+                             (size_t)m->V * 4, 8};
+    char* at[7] = {};
+    size_t total = 0, largest = 0;
+    for (size_t n : sizes) {
+      total += (n + 255) / 256 * 256;
+      largest = std::max(largest, n);
+    }
+    char* next = nullptr;
+    if (largest >= (2u << 20)) {
+      if (e == hipSuccess) e = dalloc(&next, total);
+      if (e == hipSuccess) m->tables.push_back(next);
+    }
+    for (int i = 0; i < 7 && e == hipSuccess; ++i) {
+      if (next) {
+        at[i] = next;
+        next += (sizes[i] + 255) / 256 * 256;
+      } else if (sizes[i]) {
+        e = dalloc(&at[i], sizes[i]);
+        if (e == hipSuccess) m->tables.push_back(at[i]);
+      }
+    }
+    m->P0 = (float*)at[0];
+    m->P1 = (float*)at[1];
+    (m->bf16 ? m->Wb : m->Ws) = (uint16_t*)at[2];
+    m->Wsi = m->bf16 ? nullptr : (uint16_t*)at[3];
+    m->Wi = at[4];
+    m->bias = (float*)at[5];
+    m->zscale = (float*)at[6];
+  }
   if (e == hipSuccess)
     e = launch_model_setup(embed, conv, w_out, b_out, m->V, m->C, m->Kpad, m->Vpad, m->bf16,
-                           m->P0, m->P1, m->Wf, m->Wb, m->Wi, m->bias, st);
+                           m->P0, m->P1, m->Ws, m->Wsi, m->zscale, m->Wb, m->Wi, m->bias, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) {
     tbs_model_destroy(m);
@@ -833,12 +867,7 @@ void tbs_model_destroy(tbs_model* m) {
   }
   prof_drop(m);
   for (hipEvent_t e : m->prof_pool) (void)hipEventDestroy(e);
-  (void)hipFree(m->P0);
-  (void)hipFree(m->P1);
-  (void)hipFree(m->Wf);
-  (void)hipFree(m->Wb);
-  (void)hipFree(m->Wi);
-  (void)hipFree(m->bias);
+  for (char* p : m->tables) (void)hipFree(p);
   if (m->busy) {
     if (m->busy_pending) (void)hipEventSynchronize(m->busy);
     (void)hipEventDestroy(m->busy);

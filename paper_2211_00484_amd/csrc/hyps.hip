@@ -38,7 +38,7 @@ __device__ __forceinline__ double neg_inf_d() { return -__builtin_inf(); }
 
 // Joiner rows of frame t for stream b from the hypotheses in buffer buf: the distinct
 // contexts, ascending, go to rows b * N + r (rowctx, hrow), and each row's input
-// h = tanh(enc[b][t] + ReLU(P0[a] + P1[c])) for context (a, c), fp32 or bf16 (RNE).
+// h = tanh(enc[b][t] + ReLU(P0[a] + P1[c])) for context (a, c), fp16 pairs or bf16 (RNE).
 // Every thread of the workgroup calls it.
 __device__ void hyp_rows(const ModelDev& m, const HypDev& d, int b, int t, int buf, int* s_c,
                          int* s_rc, int* s_nd) {
@@ -83,7 +83,7 @@ __device__ void hyp_rows(const ModelDev& m, const HypDev& d, int b, int t, int b
     if (m.bf16)
       reinterpret_cast<uint16_t*>(d.h)[q] = f32_to_bf16_rne(x);
     else
-      reinterpret_cast<float*>(d.h)[q] = x;
+      store_split(d.h, (o + r) * Kpad, k, x);
   }
 }
 

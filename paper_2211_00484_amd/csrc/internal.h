@@ -37,6 +37,40 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
   return (uint16_t)(u >> 16);
 }
 
+// The frame joiner's fp32 operands travel as pairs of fp16, x = high + low to about 2^-23
+// of x: h scaled by 2^14, W by a power of two per model that takes its largest magnitude
+// to [2^13, 2^14), so that high parts stay clear of fp16's limits and low parts (down to
+// 2^-24) resolve 2^-39 of the largest magnitude.  A product is then three on the fp16
+// matrix units (high x high, high x low, low x high; low x low is below 2^-22 of it).
+// Rows of h hold four values in 16 bytes (their high parts, then their low parts), W eight
+// in 32.
+constexpr float kHScale = 16384.f;
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint16_t f16_bits(_Float16 x) { return __builtin_bit_cast(uint16_t, x); }
+// (an infinite or NaN x keeps it in the high part)
+__device__ __forceinline__ void f32_split(float x, uint16_t& hi, uint16_t& lo) {
+  const _Float16 a = (_Float16)x;
+  const float r = x - (float)a;
+  hi = f16_bits(a);
+  lo = f16_bits((_Float16)(fabsf(r) < INFINITY ? r : 0.f));
+}
+// h (finite, |h| <= 1) as element k of the row at element row0 of base
+__device__ __forceinline__ void store_split(void* base, size_t row0, int k, float h) {
+  uint16_t* p = reinterpret_cast<uint16_t*>(base) + 2 * (row0 + (k & ~3)) + (k & 3);
+  const float x = h * kHScale;
+  const _Float16 a = (_Float16)x;
+  p[0] = f16_bits(a);
+  p[4] = f16_bits((_Float16)(x - (float)a));
+}
+__device__ __forceinline__ void split_pair(float h0, float h1, unsigned& hi, unsigned& lo) {
+  const f32x2 x = {h0 * kHScale, h1 * kHScale};
+  const f16x2 a = __builtin_convertvector(x, f16x2);
+  const f32x2 r = {x[0] - (float)a[0], x[1] - (float)a[1]};
+  hi = __builtin_bit_cast(unsigned, a);
+  lo = __builtin_bit_cast(unsigned, __builtin_convertvector(r, f16x2));
+}
+
 // tanh for the joiner input: (e - 1) / (e + 1), e = exp(2x), with x clamped to [-9, 9]
 // (|tanh(9)| rounds to 1 in fp32), the hardware exp and reciprocal.
 __device__ __forceinline__ float tanh_fast(float x) {
@@ -51,7 +85,10 @@ struct ModelDev {
   int bf16;
   const float* P0;          // [V][Kpad] conv tap 0 * embedding (older label)
   const float* P1;          // [V][Kpad] conv tap 1 * embedding (newer label)
-  const float* Wf;          // [Vpad][Kpad] fp32 joiner weight (fp32 mode)
+  const uint16_t* Ws;       // [Vpad][Kpad] joiner weight as fp16 pairs (fp32 mode)
+  const uint16_t* Wsi;      // [Kpad/8][2][Vpad][8] the same, high and low parts interleaved
+                            // by 16-byte k slices (small frame-joiner tiles)
+  const float* zscale;      // [0]: logit = zscale * (sum of products of scaled pairs)
   const uint16_t* Wb;       // [Vpad][Kpad] bf16 joiner weight (bf16 mode)
   const void* Wi;           // [Kpad/KQ][Vpad][KQ] W interleaved by 16-byte k slices (KQ = 4 fp32
                             // or 8 bf16), read by the per-stream kernel
@@ -85,7 +122,7 @@ struct DecodeDev {
   int* nctx;                // [B]
   int* ctx_list;            // [B][Nc], ascending
   double* offset;           // [B]
-  void* h;                  // [B*Nc][Kpad] joiner input rows tanh(enc + dec) (fp32 or bf16)
+  void* h;                  // [B*Nc][Kpad] joiner input rows tanh(enc + dec) (fp16 pairs or bf16)
   float* logits;            // [B*Nc][Vpad] (general graphs)
   float2* stats;            // [B*Nc][nvt]: (max, sum exp(z - max)) per vocabulary tile
   float* tk_z;              // [B*Nc][nvt*4][KT] trivial fast path: best logits per 16-column sub-tile
@@ -97,8 +134,9 @@ struct DecodeDev {
 };
 
 struct JoinerPlan {
-  int MB;                   // 0: GEMM tiles (shape); else 16 MB x 64 tiles
-  int shape;                // GEMM tiles: 0 = 128 x 128, 1 = 256 x 256 (bf16), 2 = 64 x 128
+  bool small;               // 16 x 64 tiles
+  bool sweep;               // sweep (n_ct column tiles x n_rt row groups); else GEMM tiles (shape)
+  int shape;                // GEMM tiles: 0 = 64 x 128, 1 = 256 x 256 (bf16)
   int n_rt, n_ct;           // row and column tiles
   int grid;                 // workgroups (XCD-interleaved tile order)
   size_t lds;               // dynamic LDS bytes
@@ -139,8 +177,8 @@ hipError_t launch_stream(const ModelDev& m, const GraphDev& g, const DecodeDev& 
 
 hipError_t launch_model_setup(const float* embed, const float* conv, const float* w_out,
                               const float* b_out, int V, int C, int Kpad, int Vpad, int bf16,
-                              float* P0, float* P1, float* Wf, uint16_t* Wb, void* Wi,
-                              float* bias, hipStream_t st);
+                              float* P0, float* P1, uint16_t* Ws, uint16_t* Wsi, float* zscale,
+                              uint16_t* Wb, void* Wi, float* bias, hipStream_t st);
 hipError_t launch_fill_i32(int* p, long long n, int v, hipStream_t st);
 // out[b] = min(max(in[b], 0), T) for b < B (device arrays)
 hipError_t launch_clamp_lengths(const int* in, int* out, int B, int T, hipStream_t st);

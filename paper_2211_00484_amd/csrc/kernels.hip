@@ -19,6 +19,7 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstddef>
 #include <cstdint>
@@ -29,6 +30,7 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((__vector_size__(8 * sizeof(__bf16))));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 constexpr unsigned long long kEmpty = ~0ull;
 
@@ -47,6 +49,7 @@ __device__ __forceinline__ float ord2f(uint32_t o) {
 }
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
+__device__ __forceinline__ f16x8 as_f16x8(uint4 v) { return __builtin_bit_cast(f16x8, v); }
 
 // Cross-lane reductions on DPP row rotations (16-lane rows) and readlane, which
 // stay in the VALU instead of taking an LDS round trip per step.
@@ -172,6 +175,14 @@ __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v)
   return r;
 }
 
+// Workgroup barrier that orders LDS accesses only: global loads and stores issued before
+// it may still be in flight.
+__device__ __forceinline__ void lds_only_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Inclusive prefix sum over the wave's 64 lanes on DPP: shifts by 1, 2, 4 and 8 within
 // each row of 16 (lanes before the shift's source add 0), then the row broadcasts of
 // lane 15 (into rows 1 and 3) and lane 31 (into rows 2 and 3); no LDS round trip.
@@ -194,19 +205,43 @@ __device__ __forceinline__ double lse_of(float M, float S) { return (double)M + 
 __device__ __forceinline__ float logp_of(float z, double lse) { return (float)((double)z - lse); }
 
 // ---------------------------------------------------------------------------
-// model setup: P0 = tap0 * E, P1 = tap1 * E (padded to Kpad), W packed to
-// [Vpad][Kpad] in fp32 or bf16, bias copied (zeros if absent).  Wi holds W once
-// more, interleaved as [Kpad / KQ][Vpad][KQ] (KQ = 16 bytes of elements: 4 fp32
-// or 8 bf16), so that 64 lanes loading 16 bytes each for 64 consecutive
-// vocabulary columns read one contiguous kilobyte (per-stream kernel).
+// model setup: P0 = tap0 * E, P1 = tap1 * E (padded to Kpad), W packed to [Vpad][Kpad]
+// for the frame joiner's GEMM tiles (bf16, or fp32 split into fp16 pairs), bias copied
+// (zeros if absent).  Wi holds W once more, interleaved as [Kpad / KQ][Vpad][KQ] (KQ = 16
+// bytes of elements: 4 fp32 or 8 bf16), so that 64 lanes loading 16 bytes each for 64
+// consecutive vocabulary columns read one contiguous kilobyte (per-stream kernels, bf16
+// small tiles); Wsi is the split W the same way, [Kpad / 8][high, low][Vpad][8].
+
+// Largest finite |W| (as bits) into wmax, which starts at 0.
+__global__ __launch_bounds__(256) void k_weight_max(const float* __restrict__ W, long long n,
+                                                    unsigned* __restrict__ wmax) {
+  unsigned v = 0;
+  for (long long i = blockIdx.x * 256ll + threadIdx.x; i < n; i += gridDim.x * 256ll) {
+    const unsigned u = __float_as_uint(W[i]) & 0x7fffffffu;
+    if (u < 0x7f800000u) v = max(v, u);
+  }
+  v = wave_max_u32(v);
+  if ((threadIdx.x & 63) == 0) atomicMax(wmax, v);
+}
+
+// Exponent s of the power of two that takes a joiner weight's largest magnitude to
+// [2^13, 2^14), within the range whose inverse (and that of h) fp32 can hold.
+__device__ __forceinline__ int split_exponent(unsigned wmax) {
+  const int e = (int)(wmax >> 23) - 127;  // wmax in [2^e, 2^(e+1)), or 0
+  return wmax == 0 ? 0 : min(13 - e, 112);
+}
 
 __global__ void k_model_setup(const float* __restrict__ E, const float* __restrict__ conv,
                               const float* __restrict__ W, const float* __restrict__ b_out, int V,
                               int C, int Kpad, int Vpad, int bf16, float* __restrict__ P0,
-                              float* __restrict__ P1, float* __restrict__ Wf,
+                              float* __restrict__ P1, uint16_t* __restrict__ Ws,
+                              uint16_t* __restrict__ Wsi, float* __restrict__ zscale,
                               uint16_t* __restrict__ Wb, void* __restrict__ Wi,
                               float* __restrict__ bias) {
   const long long n = (long long)Vpad * Kpad;
+  // zscale: the largest |W| on entry (bits, second word); z = zscale[0] * (scaled sum)
+  const int sexp = bf16 ? 0 : split_exponent(reinterpret_cast<const unsigned*>(zscale)[1]);
+  if (!bf16 && blockIdx.x == 0 && threadIdx.x == 0) zscale[0] = ldexpf(1.f / kHScale, -sexp);
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x) {
     const int v = (int)(i / Kpad), k = (int)(i - (long long)v * Kpad);
@@ -222,7 +257,14 @@ __global__ void k_model_setup(const float* __restrict__ E, const float* __restri
       Wb[i] = wb;
       reinterpret_cast<uint16_t*>(Wi)[((size_t)(k >> 3) * Vpad + v) * 8 + (k & 7)] = wb;
     } else {
-      Wf[i] = w;
+      uint16_t hi, lo;
+      f32_split(ldexpf(w, sexp), hi, lo);
+      uint16_t* row = Ws + (size_t)v * Kpad * 2 + (k >> 3) * 16 + (k & 7);
+      row[0] = hi;
+      row[8] = lo;
+      uint16_t* col = Wsi + ((size_t)(k >> 3) * 2 * Vpad + v) * 8 + (k & 7);
+      col[0] = hi;
+      col[(size_t)Vpad * 8] = lo;
       reinterpret_cast<float*>(Wi)[((size_t)(k >> 2) * Vpad + v) * 4 + (k & 3)] = w;
     }
     if (k == 0 && v < V) bias[v] = b_out ? b_out[v] : 0.f;
@@ -247,12 +289,13 @@ __global__ void k_clamp_lengths(const int* __restrict__ in, int* __restrict__ ou
 
 // Joiner input rows (Algorithm 1: decoder, IndexSelect of the encoder frame):
 // h[k] = tanh(enc[k] + ReLU(P0[a][k] + P1[b][k])) for k < C, 0 for C <= k < Kpad,
-// stored as fp32 or bf16 (RNE) at hbase + r * hstride elements (global memory or
-// LDS).  Row r reads P0/P1 at rowoff[r] = (a * Kpad, b * Kpad) and the encoder
+// stored as bf16 (RNE), fp16 pairs or fp32 at hbase + r * hstride elements (global memory
+// or LDS).  Row r reads P0/P1 at rowoff[r] = (a * Kpad, b * Kpad) and the encoder
 // row enc_rows + r * enc_stride (enc_stride = 0: one shared frame).
 // Thread tid owns columns tid, tid + NT, ... of every row (Kpad is a multiple of
 // 512); a batch's loads are all issued before any tanh.
-template <int NT, int U = 16>  // U: (row, column) elements per thread per batch
+// SPLIT: fp16 pairs in place of fp32 (rows of the frame schedule)
+template <int NT, bool SPLIT, int U = 16>  // U: (row, column) elements per thread per batch
 __device__ void write_h_rows(const ModelDev& m, const float* __restrict__ enc_rows,
                              long long enc_stride, const int2* rowoff, int nrows,
                              void* __restrict__ hbase, int hstride, int tid) {
@@ -294,6 +337,8 @@ __device__ void write_h_rows(const ModelDev& m, const float* __restrict__ enc_ro
       const size_t o = (size_t)ro[u] * hstride + k;
       if (m.bf16)
         reinterpret_cast<uint16_t*>(hbase)[o] = f32_to_bf16_rne(h);
+      else if (SPLIT)
+        store_split(hbase, (size_t)ro[u] * hstride, k, h);
       else
         reinterpret_cast<float*>(hbase)[o] = h;
     }
@@ -302,8 +347,9 @@ __device__ void write_h_rows(const ModelDev& m, const float* __restrict__ enc_ro
 
 // The same rows for C a multiple of 4, four adjacent columns per item: item i of the
 // nrows x Kpad / 4 (row, column quad) items is thread i mod NT's; a batch of U items per
-// thread issues U 16-byte loads of P0 and of P1 (all in flight at once), then U 16-byte
-// (fp32) or 8-byte (bf16) stores.  enc is one frame shared by every row.
+// thread issues U 16-byte loads of P0 and of P1 (all in flight at once), then U 8-byte (bf16)
+// or 16-byte (fp16 pairs) stores.  enc is one frame shared by every row.  (Rows of the
+// frame schedule: never fp32.)
 template <int NT, int U>
 __device__ void write_h_rows_quads(const ModelDev& m, const float* __restrict__ enc,
                                    const int2* rowoff, int nrows, void* __restrict__ hbase,
@@ -357,15 +403,20 @@ __device__ void write_h_rows_quads(const ModelDev& m, const float* __restrict__ 
 #pragma unroll
       for (int u = 0; u < U; ++u)
         if (i0 + tid + u * NT < total)
-          *reinterpret_cast<float4*>(reinterpret_cast<float*>(hbase) + (size_t)ro[u] * hstride + ko[u]) = h[u];
+        {
+          uint4 v;
+          split_pair(h[u].x, h[u].y, v.x, v.z);
+          split_pair(h[u].z, h[u].w, v.y, v.w);
+          *reinterpret_cast<uint4*>(reinterpret_cast<unsigned*>(hbase) + (size_t)ro[u] * hstride + ko[u]) = v;
+        }
     }
   }
 }
 
 // The same rows for an even C, two adjacent columns per item: thread tid owns the
 // column pairs (2 tid, 2 tid + 1), (2 tid + 2 NT, ...), ... of every row, so a batch
-// of U items issues U 8-byte loads of P0 and of P1 (all in flight at once) and U
-// 8-byte (fp32) or 4-byte (bf16) stores.  enc is one frame shared by every row.
+// of U items issues U 8-byte loads of P0 and of P1 (all in flight at once) and U 4-byte
+// (bf16) or 2 U 4-byte (fp16 pairs) stores.  enc is one frame shared by every row.
 template <int NT, int U = 16>
 __device__ void write_h_rows_pairs(const ModelDev& m, const float* __restrict__ enc,
                                    const int2* rowoff, int nrows, void* __restrict__ hbase,
@@ -423,7 +474,11 @@ __device__ void write_h_rows_pairs(const ModelDev& m, const float* __restrict__ 
 #pragma unroll
       for (int u = 0; u < U; ++u)
         if (ro[u] < nrows)
-          *reinterpret_cast<float2*>(reinterpret_cast<float*>(hbase) + (size_t)ro[u] * hstride + ko[u]) = hpair(u);
+        {
+          const float2 h = hpair(u);
+          unsigned* quad = reinterpret_cast<unsigned*>(hbase) + (size_t)ro[u] * hstride + (ko[u] & ~3) + ((ko[u] >> 1) & 1);
+          split_pair(h.x, h.y, quad[0], quad[2]);
+        }
     }
   }
 }
@@ -439,7 +494,7 @@ __global__ __launch_bounds__(256) void k_h_rows(ModelDev m, const float* __restr
   }
   __syncthreads();
   const size_t esz = m.bf16 ? 2 : 4;
-  write_h_rows<256>(m, enc_rows + (size_t)r * m.C, 0, &off, 1,
+  write_h_rows<256, true>(m, enc_rows + (size_t)r * m.C, 0, &off, 1,
                     reinterpret_cast<char*>(h) + (size_t)r * m.Kpad * esz, m.Kpad, threadIdx.x);
 }
 
@@ -469,7 +524,7 @@ __global__ __launch_bounds__(256) void k_h_rows_dense(ModelDev m, const float* _
     off = make_int2(a * m.Kpad, (c - a * m.V) * m.Kpad);
   }
   __syncthreads();
-  write_h_rows<256>(m, enc + (size_t)(g / per_enc) * enc_stride, 0, &off, 1, hrow, m.Kpad,
+  write_h_rows<256, true>(m, enc + (size_t)(g / per_enc) * enc_stride, 0, &off, 1, hrow, m.Kpad,
                     threadIdx.x);
 }
 
@@ -489,7 +544,7 @@ struct JoinArgs {
   int rows_mode;            // 1: every row < R is active
   const int* len;
   const int* nctx;
-  int t, Nc;
+  int t, B, Nc;
 };
 
 __device__ __forceinline__ bool joiner_row_active(const JoinArgs& a, int r) {
@@ -499,24 +554,102 @@ __device__ __forceinline__ bool joiner_row_active(const JoinArgs& a, int r) {
   return a.t < a.len[b] && j < a.nctx[b];
 }
 
-// Small joiner tile, for batches too small to give every compute unit a 128 x 128
-// tile: (16 * MB rows) x 64 vocabulary columns; wave w owns columns 16w..16w+15
-// and keeps its W fragment (16 columns x up to 512 of K) in registers while it
-// sweeps the tile's row blocks, whose h rows are staged once in LDS.
+// The rows of a tile: entries [r0, r0 + BM) of the batch's active rows, in (stream,
+// context slot) order, into s_row (-1 past the last); false if there are none.  Rows are
+// b * Nc + j for the j < nctx[b] contexts of a stream within its length: packing them
+// leaves no tile of the grid, which is sized for Nc rows per stream, with holes (a beam
+// keeps about half of the contexts it may).  Each thread takes consecutive streams.
+// Every thread calls it; it ends with a barrier.
+template <int NT, int BM>
+__device__ __forceinline__ bool joiner_tile_rows(const JoinArgs& a, int r0, int* s_row, int* s_wsum) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (a.rows_mode) {
+    for (int i = tid; i < BM; i += NT) s_row[i] = r0 + i < a.R ? r0 + i : -1;
+    __syncthreads();
+    return r0 < a.R;
+  }
+  const int per = (a.B + NT - 1) / NT, b0 = min(tid * per, a.B), b1 = min(b0 + per, a.B);
+  int n = 0;
+  for (int b = b0; b < b1; ++b) n += a.t < a.len[b] ? a.nctx[b] : 0;
+  for (int i = tid; i < BM; i += NT) s_row[i] = -1;
+  const int incl = (int)wave_incl_scan_u32((unsigned)n);
+  if (lane == 63) s_wsum[wave] = incl;
+  __syncthreads();
+  int pos = incl - n, total = 0;
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) {
+    const int x = s_wsum[w];
+    if (w < wave) pos += x;
+    total += x;
+  }
+  if (pos < r0 + BM && pos + n > r0)
+    for (int b = b0; b < b1; ++b) {
+      const int nb = a.t < a.len[b] ? a.nctx[b] : 0;
+      for (int j = max(0, r0 - pos); j < nb && pos + j < r0 + BM; ++j) s_row[pos + j - r0] = b * a.Nc + j;
+      pos += nb;
+    }
+  __syncthreads();
+  return r0 < total;
+}
+
+// Tile of workgroup i, which runs on XCD i mod 8.  When the column tiles divide (nearly)
+// evenly by 8, XCD x owns the column tiles x, x + 8, ... and walks row tiles in order, its
+// column tiles fastest: its W columns stay in its L2 while each h row tile is read once per
+// XCD.  Otherwise some XCDs would hold more of them (all the work, for few column tiles),
+// and the tiles go round in row-major order.
+__host__ __device__ inline int joiner_xcd_cols(int n_ct) {  // column tiles per XCD, or 0
+  const int n = (n_ct + 7) / 8;
+  return 8 * (8 * n - n_ct) <= n_ct ? n : 0;
+}
+inline int joiner_grid(int n_rt, int n_ct) {
+  const int n = joiner_xcd_cols(n_ct);
+  return (n ? 8 * n : n_ct) * n_rt;
+}
+__device__ __forceinline__ bool joiner_tile_of(int i, int n_ct, int& rt, int& ct) {
+  const int n = joiner_xcd_cols(n_ct);
+  if (n) {
+    const int slot = i >> 3;
+    rt = slot / n;
+    ct = (i & 7) + 8 * (slot - rt * n);
+  } else {
+    rt = i / n_ct;
+    ct = i - rt * n_ct;
+  }
+  return ct < n_ct;
+}
+
+// A 16-byte chunk cc of a joiner row into its LDS copy: bf16 as it is; fp16 pairs (four
+// high parts, four low parts) into the half of their eight-value group's high and low 16
+// bytes, so that an MFMA operand is one 16-byte read.
+template <bool BF16>
+__device__ __forceinline__ void stage_chunk(unsigned char* row, int cc, const uint4& v) {
+  if (BF16) {
+    *reinterpret_cast<uint4*>(row + (size_t)cc * 16) = v;
+  } else {
+    unsigned char* p = row + (size_t)(cc >> 1) * 32 + (cc & 1) * 8;
+    *reinterpret_cast<uint2*>(p) = make_uint2(v.x, v.y);
+    *reinterpret_cast<uint2*>(p + 16) = make_uint2(v.z, v.w);
+  }
+}
+
+// Small joiner tile, for batches with few tiles per compute unit: 16 rows x 64 vocabulary
+// columns; wave w owns columns 16w..16w+15 and keeps its W fragment (16 columns x up to
+// 512 of K) in registers; the tile's h rows are staged once in LDS.  (Tiles of 32 and 64
+// rows, which reuse W, measured slower at every size: fewer workgroups in flight.)
 struct JoinShared {
-  int act[64];
-  float m[4][64], s[4][64];
+  int row[16];
+  float m[4][16], s[4][16];
 };
 
-// One joiner tile (16 * MB rows x 64 vocabulary columns) of frame a.t.  Uniform
+// One joiner tile of frame a.t.  Uniform
 // across the workgroup; a tile without active rows computes nothing.
-template <bool BF16, int MB, bool TOPK>
+template <bool BF16, bool TOPK>
 __device__ __forceinline__ void joiner_tile_small(const ModelDev& m, const JoinArgs& a, int ct, int rt,
                                             unsigned char* smem, JoinShared& js) {
-  int* s_act = js.act;
-  float(*s_m)[64] = js.m;
-  float(*s_s)[64] = js.s;
-  constexpr int BM = 16 * MB;
+  int* s_row = js.row;
+  float(*s_m)[16] = js.m;
+  float(*s_s)[16] = js.s;
+  constexpr int BM = 16;
   constexpr int ESZ = BF16 ? 2 : 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r0 = rt * BM, n0 = ct * kJoinerBN;
@@ -525,15 +658,13 @@ __device__ __forceinline__ void joiner_tile_small(const ModelDev& m, const JoinA
   const int col = n0 + 16 * wave + lr;
   const bool cvalid = col < V;
 
-  if (tid < BM) s_act[tid] = joiner_row_active(a, r0 + tid);
   // W fragment of the first K chunk (registers) and the bias: issued before the
   // h staging so that all of the tile's loads are in flight together
-  // (Kpad is a multiple of 512: one chunk of W per lane is 32 float4 or 16 uint4).
-  // W is read from its interleaved copy (16-byte k slices, columns consecutive),
-  // where the 16 lanes of a k slice read 256 contiguous bytes.
-  float4 wf[BF16 ? 1 : 32];
-  uint4 wb[BF16 ? 16 : 1];
-  const uint4* __restrict__ wi = reinterpret_cast<const uint4*>(m.Wi);
+  // (Kpad is a multiple of 512: one chunk of W per lane is 16 uint4 of bf16, or of high
+  // and of low parts).  W is read from its interleaved copy (16-byte k slices, columns
+  // consecutive), where the 16 lanes of a k slice read 256 contiguous bytes.
+  uint4 wb[16], wl[BF16 ? 1 : 16];
+  const uint4* __restrict__ wi = reinterpret_cast<const uint4*>(BF16 ? m.Wi : (const void*)m.Wsi);
   const size_t Vp = (size_t)m.Vpad;
   auto load_w = [&](int kc) {
     if (BF16) {
@@ -544,53 +675,56 @@ __device__ __forceinline__ void joiner_tile_small(const ModelDev& m, const JoinA
         wb[2 * s + 1] = wi[(q0 + 8 * s + 1) * Vp + col];
       }
     } else {
-      const size_t q0 = (size_t)(kc / 4 + lg);
+      const size_t q0 = (size_t)(kc / 8 + lg);
 #pragma unroll
-      for (int s = 0; s < 32; ++s) {
-        const uint4 v = wi[(q0 + 4 * s) * Vp + col];
-        wf[s] = make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z),
-                            __uint_as_float(v.w));
+      for (int s = 0; s < 16; ++s) {
+        wb[s] = wi[2 * (q0 + 4 * s) * Vp + col];
+        wl[BF16 ? 0 : s] = wi[(2 * (q0 + 4 * s) + 1) * Vp + col];
       }
     }
   };
   load_w(0);
+  const float zscale = BF16 ? 1.f : m.zscale[0];
   const float bias = cvalid ? m.bias[col] : 0.f;
-  __syncthreads();
-  int any = 0;
-#pragma unroll
-  for (int i = 0; i < BM; ++i) any |= s_act[i];
-  if (!any) return;  // uniform across the workgroup: nothing to compute in this tile
+  // (rows of the tile's own slots: packing the active rows, as the larger tiles do, costs
+  // this one more latency than the tiles it saves)
+  const int act = tid < BM ? (int)joiner_row_active(a, r0 + tid) : 0;
+  if (tid < BM) s_row[tid] = act ? r0 + tid : -1;
+  if (!__syncthreads_or(act)) return;  // uniform: no row in this tile
 
   // stage the tile's h rows in LDS (16-byte chunks, all loads in flight together)
   const int ldk = Kpad + (BF16 ? 8 : 4);             // row stride in elements (16-byte pad)
   const int cpr = Kpad * ESZ / 16;                   // 16-byte chunks per row
   const int nchunk = BM * cpr;
-  const char* hsrc = reinterpret_cast<const char*>(a.h) + (size_t)r0 * Kpad * ESZ;
+  const uint4* hsrc = reinterpret_cast<const uint4*>(a.h);
   for (int base = tid; base < nchunk; base += 256 * 16) {
     uint4 v[16];
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const int c = base + u * 256;
       v[u] = make_uint4(0, 0, 0, 0);
-      if (c < nchunk && s_act[c / cpr]) v[u] = reinterpret_cast<const uint4*>(hsrc)[c];
+      if (c < nchunk) {
+        const int r = c / cpr, row = s_row[r];
+        if (row >= 0) v[u] = hsrc[(size_t)row * cpr + (c - r * cpr)];
+      }
     }
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const int c = base + u * 256;
       if (c < nchunk) {
         const int r = c / cpr, cc = c - r * cpr;
-        *reinterpret_cast<uint4*>(smem + (size_t)r * ldk * ESZ + (size_t)cc * 16) = v[u];
+        stage_chunk<BF16>(smem + (size_t)r * ldk * ESZ, cc, v[u]);
       }
     }
   }
 
-  // Four accumulator chains per row block, and consecutive MFMAs rotate over
-  // (row block, chain), so no MFMA waits for the one before it.
-  f32x4 acc[MB][4];
+  // Several accumulator chains per row block, and consecutive MFMAs rotate over (row
+  // block, chain), so no MFMA waits for the one before it: four for bf16; for fp16 pairs
+  // the sums of high x high, high x low and low x high, over even and odd k-steps each.
+  constexpr int NC = BF16 ? 4 : 6;
+  f32x4 acc[NC];
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) acc[mb][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c = 0; c < NC; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   for (int kc = 0; kc < Kpad; kc += 512) {
     if (kc > 0) load_w(kc);  // later K chunks (C > 512)
@@ -599,31 +733,26 @@ __device__ __forceinline__ void joiner_tile_small(const ModelDev& m, const JoinA
       const uint16_t* hb = reinterpret_cast<const uint16_t*>(smem) + (size_t)lr * ldk + kc + 16 * lg;
 #pragma unroll
       for (int s = 0; s < 8; ++s) {
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-          const uint16_t* hr = hb + (size_t)mb * 16 * ldk + s * 64;
-          const uint4 a0 = *reinterpret_cast<const uint4*>(hr);
-          const uint4 a1 = *reinterpret_cast<const uint4*>(hr + 8);
-          f32x4& c0 = acc[mb][(2 * s) & 3];
-          f32x4& c1 = acc[mb][(2 * s + 1) & 3];
-          c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a0), as_bf16x8(wb[2 * s]), c0, 0, 0,
-                                                       0);
-          c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a1), as_bf16x8(wb[2 * s + 1]), c1,
-                                                       0, 0, 0);
-        }
+        const uint16_t* hr = hb + s * 64;
+        const uint4 a0 = *reinterpret_cast<const uint4*>(hr);
+        const uint4 a1 = *reinterpret_cast<const uint4*>(hr + 8);
+        f32x4& c0 = acc[(2 * s) & 3];
+        f32x4& c1 = acc[(2 * s + 1) & 3];
+        c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a0), as_bf16x8(wb[2 * s]), c0, 0, 0, 0);
+        c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a1), as_bf16x8(wb[2 * s + 1]), c1, 0, 0, 0);
       }
     } else {
-      const float* hs = reinterpret_cast<const float*>(smem) + (size_t)lr * ldk + kc + 4 * lg;
+      const uint16_t* hs = reinterpret_cast<const uint16_t*>(smem) + 2 * ((size_t)lr * ldk + kc + 8 * lg);
 #pragma unroll
-      for (int s = 0; s < 32; ++s) {
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-          const float4 av = *reinterpret_cast<const float4*>(hs + (size_t)mb * 16 * ldk + s * 16);
-          acc[mb][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, wf[s].x, acc[mb][0], 0, 0, 0);
-          acc[mb][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, wf[s].y, acc[mb][1], 0, 0, 0);
-          acc[mb][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.z, wf[s].z, acc[mb][2], 0, 0, 0);
-          acc[mb][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.w, wf[s].w, acc[mb][3], 0, 0, 0);
-        }
+      for (int s = 0; s < 16; ++s) {
+        const uint16_t* hr = hs + 64 * s;
+        const f16x8 ah = as_f16x8(*reinterpret_cast<const uint4*>(hr));
+        const f16x8 al = as_f16x8(*reinterpret_cast<const uint4*>(hr + 8));
+        const f16x8 bh = as_f16x8(wb[s]), bl = as_f16x8(wl[BF16 ? 0 : s]);
+        f32x4* c = acc + (NC == 6 ? 3 * (s & 1) : 0);
+        c[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh, c[0], 0, 0, 0);
+        c[2] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, bh, c[2], 0, 0, 0);
+        c[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bl, c[1], 0, 0, 0);
       }
     }
   }
@@ -631,105 +760,95 @@ __device__ __forceinline__ void joiner_tile_small(const ModelDev& m, const JoinA
   // epilogue.  First everything that needs the workgroup barrier (per-row max
   // and sum exp over the tile, combined across the 4 waves in LDS); the global
   // stores come after it, so the barrier never waits on them.
-  float zr[MB][4];
+  float zr[4];
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = mb * 16 + 4 * lg + i;  // the 16 lanes of a DPP row share this row
-      const float zs = (acc[mb][0][i] + acc[mb][1][i]) + (acc[mb][2][i] + acc[mb][3][i]);
-      const float z = cvalid ? zs + bias : -INFINITY;
-      zr[mb][i] = z;
-      const float mx = row16_max(z);
-      const float e = row16_sum(cvalid ? expf(z - mx) : 0.f);
-      if (lr == 0) {
-        s_m[wave][row] = mx;
-        s_s[wave][row] = e;
-      }
+  for (int i = 0; i < 4; ++i) {
+    const int row = 4 * lg + i;  // the 16 lanes of a DPP row share this row
+    const f32x4* c = acc;
+    const float zs = BF16 ? (c[0][i] + c[1][i]) + (c[2][i] + c[3][i])
+                          : (((c[1][i] + c[2][i]) + (c[NC - 2][i] + c[NC - 1][i])) +
+                             (c[0][i] + c[NC - 3][i])) * zscale;
+    const float z = cvalid ? zs + bias : -INFINITY;
+    zr[i] = z;
+    const float mx = row16_max(z);
+    const float e = row16_sum(cvalid ? expf(z - mx) : 0.f);
+    if (lr == 0) {
+      s_m[wave][row] = mx;
+      s_s[wave][row] = e;
     }
   }
   __syncthreads();
-  if (tid < BM && s_act[tid]) {
+  if (tid < BM && s_row[tid] >= 0) {
     float M = s_m[0][tid];
     for (int w = 1; w < 4; ++w) M = fmaxf(M, s_m[w][tid]);
     float S = 0.f;
     for (int w = 0; w < 4; ++w) S += s_s[w][tid] == 0.f ? 0.f : s_s[w][tid] * expf(s_m[w][tid] - M);
-    a.stats[(size_t)(r0 + tid) * nvt + ct] = make_float2(M, S);
+    a.stats[(size_t)s_row[tid] * nvt + ct] = make_float2(M, S);
   }
   // logits (general graphs) or each row's best KT labels per 16-column sub-tile
   // (trivial graph), found with DPP row reductions
   const int nsub = nvt * (kJoinerBN / 16);
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = mb * 16 + 4 * lg + i;
-      const float z = zr[mb][i];
-      const bool act = s_act[row];
-      if (!TOPK) {
-        if (act && cvalid) a.logits[(size_t)(r0 + row) * (nvt * kJoinerBN) + col] = z;
-      } else {
-        unsigned long long key = (cvalid && col >= 1)
-                                     ? ((unsigned long long)f2ord(z) << 32) | (0xffffffffu - (unsigned)col)
-                                     : 0ull;
-        const size_t ob = ((size_t)(r0 + row) * nsub + ct * (kJoinerBN / 16) + wave) * a.KT;
-        for (int q = 0; q < a.KT; ++q) {
-          const unsigned long long best = row16_max_u64(key);
-          if (act && best != 0ull && key == best) {
-            a.tk_z[ob + q] = z;
-            a.tk_c[ob + q] = col;
-          }
-          if (act && best == 0ull && lr == 0) {
-            a.tk_z[ob + q] = -INFINITY;
-            a.tk_c[ob + q] = -1;
-          }
-          if (key == best) key = 0ull;
+  for (int i = 0; i < 4; ++i) {
+    const int row = s_row[4 * lg + i];
+    const float z = zr[i];
+    const bool act = row >= 0;
+    if (!TOPK) {
+      if (act && cvalid) a.logits[(size_t)row * (nvt * kJoinerBN) + col] = z;
+    } else {
+      unsigned long long key = (cvalid && col >= 1)
+                                   ? ((unsigned long long)f2ord(z) << 32) | (0xffffffffu - (unsigned)col)
+                                   : 0ull;
+      const size_t ob = ((size_t)max(row, 0) * nsub + ct * (kJoinerBN / 16) + wave) * a.KT;
+      for (int q = 0; q < a.KT; ++q) {
+        const unsigned long long best = row16_max_u64(key);
+        if (act && best != 0ull && key == best) {
+          a.tk_z[ob + q] = z;
+          a.tk_c[ob + q] = col;
         }
-        if (act && ct == 0 && wave == 0 && lr == 0) a.z0[r0 + row] = z;
+        if (act && best == 0ull && lr == 0) {
+          a.tk_z[ob + q] = -INFINITY;
+          a.tk_c[ob + q] = -1;
+        }
+        if (key == best) key = 0ull;
       }
+      if (act && ct == 0 && wave == 0 && lr == 0) a.z0[row] = z;
     }
   }
 }
 
-template <bool BF16, int MB, bool TOPK>
+template <bool BF16, bool TOPK>
 __global__ __launch_bounds__(256) void k_joiner_small(ModelDev m, JoinArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ JoinShared js;
-  // Workgroup i runs on XCD i mod 8.  XCD x owns the column tiles x, x + 8, ...
-  // and walks row tiles in order, its column tiles fastest: its W columns stay
-  // in its L2 while each h row tile is read once per XCD.
-  const int bid = blockIdx.x, xcd = bid & 7, slot = bid >> 3;
-  const int ncx = (a.n_ct + 7) >> 3;
-  const int rt = slot / ncx, ct = xcd + 8 * (slot - rt * ncx);
-  if (ct >= a.n_ct) return;
-  joiner_tile_small<BF16, MB, TOPK>(m, a, ct, rt, smem, js);
+  int rt, ct;
+  if (!joiner_tile_of(blockIdx.x, a.n_ct, rt, ct)) return;
+  joiner_tile_small<BF16, TOPK>(m, a, ct, rt, smem, js);
 }
 
 constexpr float kLog2e = 1.44269504088896341f;
 
 // Joiner GEMM tile: BM = 32 MBW rows x BN = 64 WN vocabulary columns, 2 x WN waves,
 // each wave 16 MBW rows x 64 columns (MBW x 4 MFMA blocks of 16 x 16):
-//  - 128 x 128 (MBW = 4, WN = 2; four waves), for batches with at least four such
-//    tiles per compute unit;
-//  - 64 x 128 (MBW = 2, WN = 2; four waves, three workgroups per compute unit), for
-//    batches with one to four 128 x 128 tiles per compute unit, which it splits into
-//    finer, more evenly spread parts;
+//  - 64 x 128 (MBW = 2, WN = 2; four waves, three workgroups per compute unit);
 //  - 256 x 256 (MBW = 8, WN = 4; eight waves), for bf16 batches with several such
-//    tiles per compute unit: half the operand bytes per product of the 128 tile, and
+//    tiles per compute unit: half the operand bytes per product of a 128 x 128 tile, and
 //    a quarter fewer LDS fragment reads per MFMA.
-// Both operands go through LDS in K slices of 128 bytes per row (64 bf16 or 32 fp32
-// values), two buffers deep, one barrier per slice.  The 128 and 64 tiles keep slices
-// s + 1 and s + 2 in flight to registers during the MFMAs of slice s; the 256 tile,
-// whose slices hold twice the MFMAs, keeps slice s + 1.  A wave's 64 columns are one
+// fp32 operands come as fp16 pairs (internal.h), three MFMAs per product: 16 times the
+// rate of the fp32 MFMA for three times the instructions, with a smaller error against
+// 64 bits than 512 fp32 additions (V = 5,000, 4,000 rows: 9e-8 of the log-probabilities
+// against 2.5e-7).
+// Both operands go through LDS in K slices of 128 bytes per row (64 bf16 values or 32
+// pairs), two buffers deep, one barrier per slice.  The bf16 64-row tile keeps slices
+// s + 1 and s + 2 in flight to registers during the MFMAs of slice s; the others, whose
+// slices hold two or three times the MFMAs, keep slice s + 1.  A wave's 64 columns are one
 // vocabulary tile, so its epilogue produces that tile's (max, sum exp) per row and
 // either the logits or each row's best labels per 16-column sub-tile.
-constexpr int kJBM = 128, kJBN = 128;          // the 128 tile: rows, columns
+constexpr int kJBN = 128;                      // the 64 x 128 tile: columns
 constexpr int kJSlice = 128;                   // bytes of K per row and slice
 constexpr int kJRow = kJSlice;                 // LDS row stride (16-byte chunks swizzled per row)
-constexpr int kJStage = (kJBM + kJBN) * kJRow; // bytes per buffer: A rows, then B rows
-constexpr size_t kJLds = 2 * (size_t)kJStage;  // 65,536 bytes
-constexpr int kJHalfBM = 64;                   // the 64 x 128 tile
-constexpr size_t kJHalfLds = 2 * (size_t)(kJHalfBM + kJBN) * kJRow;  // 49,152 bytes
+constexpr int kJHalfBM = 64;                   // its rows
+constexpr size_t kJHalfLds = 2 * (size_t)(kJHalfBM + kJBN) * kJRow;  // two buffers: 49,152 bytes
 constexpr int kJWideBM = 256, kJWideBN = 256;  // the 256 tile
 constexpr size_t kJWideLds = 2 * (size_t)(kJWideBM + kJWideBN) * kJRow;  // 131,072 bytes
 // LDS chunk swizzle: chunk k of a row with index r mod 16 = l sits at slot k ^ jswz(l).
@@ -739,24 +858,18 @@ constexpr size_t kJWideLds = 2 * (size_t)(kJWideBM + kJWideBN) * kJRow;  // 131,
 __device__ __forceinline__ int jswz(int l) { return (l & 7) ^ ((l >> 3) & 1); }
 
 template <bool BF16, bool TOPK, int WN, int MBW>
-__global__ __launch_bounds__(128 * WN) void k_joiner(ModelDev m, JoinArgs a) {
+__global__ __launch_bounds__(128 * WN, MBW == 2 ? 3 : 1) void k_joiner(ModelDev m, JoinArgs a) {
   constexpr int NT = 128 * WN, BM = 32 * MBW, BN = 64 * WN;
   constexpr int STAGE = (BM + BN) * kJRow;
-  constexpr bool DEEP = MBW <= 4;  // two slices in flight (else one)
+  constexpr bool DEEP = MBW == 2 && BF16;  // two slices in flight (else one)
   constexpr int UA = BM * 8 / NT, UB = BN * 8 / NT;  // 16-byte chunks per thread and slice
   static_assert(UA * NT == BM * 8 && UB * NT == BN * 8 && UA <= UB, "slice loads");
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ int s_act[BM];
+  __shared__ int s_row[BM], s_wsum[NT / 64];
   const int bid = blockIdx.x, xcd = bid & 7, slot = bid >> 3;
   int rt, ct;
   if (WN == 2) {
-    // Workgroup i runs on XCD i mod 8.  XCD x owns the column tiles x, x + 8, ...
-    // and walks row tiles in order, its column tiles fastest: its W columns stay
-    // in its L2 while each h row tile is read once per XCD.
-    const int ncx = (a.n_ct + 7) >> 3;
-    rt = slot / ncx;
-    ct = xcd + 8 * (slot - rt * ncx);
-    if (ct >= a.n_ct) return;
+    if (!joiner_tile_of(bid, a.n_ct, rt, ct)) return;
   } else {
     // Tiles in row-major order, tile q on XCD q mod 8: with a column-tile count that
     // is not a multiple of 8, each XCD still gets an equal share, and sees only the
@@ -773,39 +886,43 @@ __global__ __launch_bounds__(128 * WN) void k_joiner(ModelDev m, JoinArgs a) {
   const int r0 = rt * BM, c0 = ct * BN;
   const int Kpad = m.Kpad, V = m.V, Vpad = m.Vpad, nvt = a.nvt;
   const int vt = WN * ct + wc;  // this wave's vocabulary tile
-  const int act = tid < BM ? (int)joiner_row_active(a, r0 + tid) : 0;
-  if (tid < BM) s_act[tid] = act;
-  if (!__syncthreads_or(act)) return;  // uniform: no active row in this tile
+  if (!joiner_tile_rows<NT, BM>(a, r0, s_row, s_wsum)) return;  // uniform: no row in this tile
   // the epilogue's bias values, requested now so that their round trip is hidden
   // behind the main loop (clamped: past the vocabulary they are never used)
+  const float zscale = BF16 ? 1.f : m.zscale[0];
   float bias_r[4];
 #pragma unroll
   for (int nb = 0; nb < 4; ++nb) bias_r[nb] = m.bias[min(64 * vt + 16 * nb + lr, V - 1)];
 
   // slice loads: UA (h) and UB (W) chunks of 16 bytes per thread (BM and BN rows x 8 chunks)
   const char* hsrc = reinterpret_cast<const char*>(a.h);
-  const char* wsrc = BF16 ? reinterpret_cast<const char*>(m.Wb) : reinterpret_cast<const char*>(m.Wf);
+  const char* wsrc = reinterpret_cast<const char*>(BF16 ? m.Wb : m.Ws);
   const size_t rowb = (size_t)Kpad * ESZ;
   const unsigned rowb32 = (unsigned)rowb;  // h and W each stay below 4 GiB (checked at launch)
+  // byte offsets of this thread's h and W chunks in slice 0 (32 bits, from the uniform
+  // bases).  Rows past the tile's last or the padded vocabulary read a valid row: their
+  // products land only in rows and columns the epilogue never writes.  (No branches
+  // around the loads, so their waits stay exact.)
+  unsigned ha[UA], wa[UB];
+#pragma unroll
+  for (int u = 0; u < UB; ++u) {
+    const int c = tid + NT * u, row = c >> 3, part = c & 7;
+    wa[u] = (unsigned)min(c0 + row, Vpad - 1) * rowb32 + part * 16;
+    if (u < UA) ha[u < UA ? u : 0] = (unsigned)max(s_row[row], s_row[0]) * rowb32 + part * 16;
+  }
   // slices in flight: register sets 0 and 1 (set 1 only with DEEP)
   uint4 ra0[UA], rb0[UB], ra1[UA], rb1[UB];
   auto gload = [&](int s, int set) {
 #pragma unroll
     for (int u = 0; u < UB; ++u) {
-      const int c = tid + NT * u, row = c >> 3, part = c & 7;
-      const size_t off = (size_t)s * kJSlice + part * 16;
-      // Rows past the batch or the padded vocabulary read the last valid row: their
-      // products land only in rows and columns the epilogue never writes.  (No
-      // branches around the loads, so their waits stay exact.)
-      // (32-bit offsets from the uniform bases: one register per load address)
-      const int hr = min(r0 + row, a.R - 1), wr_ = min(c0 + row, Vpad - 1);
-      const uint4 vb = *reinterpret_cast<const uint4*>(wsrc + ((unsigned)wr_ * rowb32 + (unsigned)off));
+      const unsigned off = (unsigned)(s * kJSlice);
+      const uint4 vb = *reinterpret_cast<const uint4*>(wsrc + (wa[u] + off));
       if (set == 0)
         rb0[u] = vb;
       else
         rb1[u] = vb;
       if (u < UA) {
-        const uint4 va = *reinterpret_cast<const uint4*>(hsrc + ((unsigned)hr * rowb32 + (unsigned)off));
+        const uint4 va = *reinterpret_cast<const uint4*>(hsrc + (ha[u < UA ? u : 0] + off));
         if (set == 0)
           ra0[u < UA ? u : 0] = va;
         else
@@ -819,31 +936,44 @@ __global__ __launch_bounds__(128 * WN) void k_joiner(ModelDev m, JoinArgs a) {
     for (int u = 0; u < UB; ++u) {
       const int c = tid + NT * u, row = c >> 3, part = c & 7;
       const int slot = (part ^ jswz(row & 15)) * 16;
-      if (u < UA)
-        *reinterpret_cast<uint4*>(base + (size_t)row * kJRow + slot) =
-            set == 0 ? ra0[u < UA ? u : 0] : ra1[u < UA ? u : 0];
+      if (u < UA) {
+        const uint4 v = set == 0 ? ra0[u < UA ? u : 0] : ra1[u < UA ? u : 0];
+        if (BF16) {
+          *reinterpret_cast<uint4*>(base + (size_t)row * kJRow + slot) = v;
+        } else {  // four high parts, four low parts: halves of the group's two chunks
+          unsigned char* p = base + (size_t)row * kJRow + ((part & 6) ^ jswz(row & 15)) * 16 + (part & 1) * 8;
+          unsigned char* q = base + (size_t)row * kJRow + ((part | 1) ^ jswz(row & 15)) * 16 + (part & 1) * 8;
+          *reinterpret_cast<uint2*>(p) = make_uint2(v.x, v.y);
+          *reinterpret_cast<uint2*>(q) = make_uint2(v.z, v.w);
+        }
+      }
       *reinterpret_cast<uint4*>(base + (size_t)(BM + row) * kJRow + slot) = set == 0 ? rb0[u] : rb1[u];
     }
   };
-  f32x4 acc[MBW][4];
+  // (fp16 pairs: the high x high products and the rest in chains of their own)
+  f32x4 acc[MBW][4], acc2[BF16 ? 1 : MBW][4];
 #pragma unroll
   for (int mb = 0; mb < MBW; ++mb)
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int nb = 0; nb < 4; ++nb) {
+      acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      acc2[BF16 ? 0 : mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
   // one slice of MFMAs from LDS buffer buf; fragments: lane (lr, lg) reads 16 bytes
-  // of row lr of a block at byte 64 j + 16 lg of the slice (bf16: k-step j of 32;
-  // fp32: group j of 16, the four values feeding four k-steps)
+  // of row lr of a block, of a bf16 slice (64 values) at byte 64 j + 16 lg (k-step j), of
+  // an fp16-pair slice (32 values, one k-step) at byte 32 lg + 16 j (j = 0: the high
+  // parts, 1: the low parts)
   auto compute = [&](int buf) {
     const unsigned char* base = smem + (size_t)buf * STAGE;
     const unsigned char* abase = base + (size_t)(16 * MBW * wr + lr) * kJRow;
     const unsigned char* bbase = base + (size_t)(BM + 64 * wc + lr) * kJRow;
-    const int cs = (lg ^ jswz(lr)) * 16;  // chunk lg (j = 0) or 4 + lg (j = 1), swizzled
+    if constexpr (BF16) {
+      const int cs = (lg ^ jswz(lr)) * 16;  // chunk lg (j = 0) or 4 + lg (j = 1), swizzled
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      uint4 fa[MBW], fb[4];
+      for (int j = 0; j < 2; ++j) {
+        uint4 fa[MBW], fb[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) fb[q] = *reinterpret_cast<const uint4*>(bbase + (size_t)16 * q * kJRow + (cs ^ (64 * j)));
-      if (BF16) {
+        for (int q = 0; q < 4; ++q) fb[q] = *reinterpret_cast<const uint4*>(bbase + (size_t)16 * q * kJRow + (cs ^ (64 * j)));
         // row blocks in groups of 4: with 8 row blocks, the fragments of the second
         // group are read after the first group's MFMAs (fewer live registers)
         constexpr int GB = MBW < 4 ? MBW : 4;
@@ -860,20 +990,28 @@ __global__ __launch_bounds__(128 * WN) void k_joiner(ModelDev m, JoinArgs a) {
                                                                     acc[mb][nb], 0, 0, 0);
           if (MBW > 4) __builtin_amdgcn_sched_barrier(0);
         }
-      } else {
+      }
+    } else {
+      const int cs = ((2 * lg) ^ jswz(lr)) * 16;  // chunk 2 lg (high) or 2 lg + 1 (low), swizzled
+      f16x8 bh[4], bl[4];
 #pragma unroll
-        for (int q = 0; q < MBW; ++q)
-          fa[q] = *reinterpret_cast<const uint4*>(abase + (size_t)16 * q * kJRow + (cs ^ (64 * j)));
+      for (int q = 0; q < 4; ++q) {
+        bh[q] = as_f16x8(*reinterpret_cast<const uint4*>(bbase + (size_t)16 * q * kJRow + cs));
+        bl[q] = as_f16x8(*reinterpret_cast<const uint4*>(bbase + (size_t)16 * q * kJRow + (cs ^ 16)));
+      }
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+      for (int mb = 0; mb < MBW; ++mb) {
+        const f16x8 ah = as_f16x8(*reinterpret_cast<const uint4*>(abase + (size_t)16 * mb * kJRow + cs));
+        const f16x8 al = as_f16x8(*reinterpret_cast<const uint4*>(abase + (size_t)16 * mb * kJRow + (cs ^ 16)));
 #pragma unroll
-          for (int mb = 0; mb < MBW; ++mb)
+        for (int nb = 0; nb < 4; ++nb)
+          acc2[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, bh[nb], acc2[mb][nb], 0, 0, 0);
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb) {
-              const float av = __uint_as_float(u == 0 ? fa[mb].x : u == 1 ? fa[mb].y : u == 2 ? fa[mb].z : fa[mb].w);
-              const float bv = __uint_as_float(u == 0 ? fb[nb].x : u == 1 ? fb[nb].y : u == 2 ? fb[nb].z : fb[nb].w);
-              acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc[mb][nb], 0, 0, 0);
-            }
+        for (int nb = 0; nb < 4; ++nb)
+          acc2[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bl[nb], acc2[mb][nb], 0, 0, 0);
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+          acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh[nb], acc[mb][nb], 0, 0, 0);
       }
     }
   };
@@ -941,13 +1079,14 @@ __global__ __launch_bounds__(128 * WN) void k_joiner(ModelDev m, JoinArgs a) {
     for (int mb = 0; mb < MBW; ++mb) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int row = 16 * MBW * wr + 16 * mb + 4 * lg + i;  // the 16 lanes of a DPP row share it
-        const bool ract = s_act[row];
+        // (the 16 lanes of a DPP row share a row)
+        const int row = s_row[16 * MBW * wr + 16 * mb + 4 * lg + i];
+        const bool ract = row >= 0;
         float z[4];
         float mx = -INFINITY;
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb) {
-          z[nb] = cvalid[nb] ? acc[mb][nb][i] + bias[nb] : -INFINITY;
+          z[nb] = cvalid[nb] ? (BF16 ? acc[mb][nb][i] : (acc[mb][nb][i] + acc2[BF16 ? 0 : mb][nb][i]) * zscale) + bias[nb] : -INFINITY;
           mx = fmaxf(mx, z[nb]);
         }
         const float M = row16_max(mx);
@@ -958,18 +1097,18 @@ __global__ __launch_bounds__(128 * WN) void k_joiner(ModelDev m, JoinArgs a) {
         for (int nb = 0; nb < 4; ++nb)
           e += cvalid[nb] ? __builtin_amdgcn_exp2f((z[nb] - M) * kLog2e) : 0.f;
         const float S = row16_sum(e);
-        if (ract && lr == 0) a.stats[(size_t)(r0 + row) * nvt + vt] = make_float2(M, S);
+        if (ract && lr == 0) a.stats[(size_t)row * nvt + vt] = make_float2(M, S);
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb) {
           const int col = 64 * vt + 16 * nb + lr;
           if (!TOPK) {
-            if (ract && cvalid[nb]) a.logits[(size_t)(r0 + row) * (nvt * kJoinerBN) + col] = z[nb];
+            if (ract && cvalid[nb]) a.logits[(size_t)row * (nvt * kJoinerBN) + col] = z[nb];
           } else {
             // each row's best KT labels of this 16-column sub-tile (DPP row reductions)
             unsigned long long key = (cvalid[nb] && col >= 1)
                                          ? ((unsigned long long)f2ord(z[nb]) << 32) | (0xffffffffu - (unsigned)col)
                                          : 0ull;
-            const size_t ob = ((size_t)(r0 + row) * nsub + vt * (kJoinerBN / 16) + nb) * a.KT;
+            const size_t ob = ((size_t)max(row, 0) * nsub + vt * (kJoinerBN / 16) + nb) * a.KT;
             for (int q = 0; q < a.KT; ++q) {
               const unsigned long long best = row16_max_u64(key);
               if (ract && best != 0ull && key == best) {
@@ -984,7 +1123,7 @@ __global__ __launch_bounds__(128 * WN) void k_joiner(ModelDev m, JoinArgs a) {
             }
           }
         }
-        if (TOPK && ract && vt == 0 && lr == 0) a.z0[r0 + row] = z[0];
+        if (TOPK && ract && vt == 0 && lr == 0) a.z0[row] = z[0];
       }
     }
   };
@@ -992,6 +1131,235 @@ __global__ __launch_bounds__(128 * WN) void k_joiner(ModelDev m, JoinArgs a) {
     epilogue(std::true_type{});
   else
     epilogue(std::false_type{});
+}
+
+// Joiner sweep, for C <= 512 and more rows than the small tiles suit: a workgroup of eight
+// waves keeps the weights of its columns in registers (a wave: 16 columns of fp16 pairs or
+// 32 of bf16, K = 512, 128 registers) and runs blocks of 16 rows past them, the next
+// block's h rows on their way to the other LDS buffer meanwhile.  Every h row is then read
+// once per 128 (256) columns and W once per workgroup, no operand is loaded twice by a
+// wave, and a logit's products go to several short accumulator chains (as in the small
+// tile, whose error it has; the GEMM tiles' single chain of 48 loses twice as much).
+// Bound: per block the LDS gives each wave its 2 KB (1 KB) of h per k-step, which takes as
+// long as the step's MFMAs.  Grid: column tiles x row groups, one workgroup per compute
+// unit; a group takes an equal, consecutive share of the batch's blocks.
+constexpr int kSweepThreads = 512;
+constexpr int kSweepK = 512;
+constexpr int kSweepMaxRows = 8192;  // rows per group (packed row list in LDS)
+
+template <bool BF16>
+constexpr int kSweepCols = BF16 ? 256 : 128;
+template <bool BF16>
+constexpr int kSweepStride = kSweepK * (BF16 ? 2 : 4) + 16;  // LDS bytes per h row
+
+// DENSE: every row of the batch is active (no packing)
+template <bool BF16, bool TOPK, bool DENSE>
+__global__ __launch_bounds__(kSweepThreads) void k_joiner_sweep(ModelDev m, JoinArgs a) {
+  constexpr int NT = kSweepThreads, NB = BF16 ? 2 : 1;  // 16-column blocks per wave
+  constexpr int NC = BF16 ? 2 : 6;                      // accumulator chains per block
+  constexpr int STRIDE = kSweepStride<BF16>, BUF = 16 * STRIDE;
+  constexpr int CPR = kSweepK * (BF16 ? 2 : 4) / 16;    // 16-byte chunks per h row
+  constexpr int U = 16 * CPR / NT;                      // chunks per thread and block
+  constexpr int NVT = kSweepCols<BF16> / kJoinerBN;     // vocabulary tiles per workgroup
+  extern __shared__ __align__(16) unsigned char smem[];
+  int* list = reinterpret_cast<int*>(smem + 2 * BUF);   // packed rows (not DENSE)
+  __shared__ int s_wsum[NT / 64];
+  __shared__ float s_m[2][8][16], s_s[2][8][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lr = lane & 15, lg = lane >> 4;
+  const int V = m.V, nvt = a.nvt;
+  const int ct = blockIdx.x % a.n_ct, grp = blockIdx.x / a.n_ct;
+  const int col0 = ct * kSweepCols<BF16> + wave * 16 * NB + lr;
+  // (columns past the padded vocabulary read its last one and are never written)
+  uint4 wb[NB][16], wl[BF16 ? 1 : 16];
+  {
+    const uint4* __restrict__ wi = reinterpret_cast<const uint4*>(BF16 ? m.Wi : (const void*)m.Wsi);
+    const size_t Vp = (size_t)m.Vpad;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const int col = min(col0 + 16 * nb, m.Vpad - 1);
+#pragma unroll
+      for (int s = 0; s < 16; ++s) {
+        if (BF16) {
+          wb[nb][s] = wi[(size_t)(4 * s + lg) * Vp + col];
+        } else {
+          wb[nb][s] = wi[(size_t)(2 * (4 * s + lg)) * Vp + col];
+          wl[BF16 ? 0 : s] = wi[(size_t)(2 * (4 * s + lg) + 1) * Vp + col];
+        }
+      }
+    }
+  }
+  const float zscale = BF16 ? 1.f : m.zscale[0];
+  bool cvalid[NB];
+  float bias[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    cvalid[nb] = col0 + 16 * nb < V;
+    bias[nb] = m.bias[min(col0 + 16 * nb, V - 1)];
+  }
+
+  // this group's rows: blocks [grp * q, (grp + 1) * q) of the active rows, q blocks each
+  int total = a.R, per = 0, b0 = 0, b1 = 0, pos = 0;
+  if (!DENSE) {  // pack the active rows in (stream, context slot) order
+    per = (a.B + NT - 1) / NT;
+    b0 = min(tid * per, a.B);
+    b1 = min(b0 + per, a.B);
+    int n = 0;
+    for (int b = b0; b < b1; ++b) n += a.t < a.len[b] ? a.nctx[b] : 0;
+    const int incl = (int)wave_incl_scan_u32((unsigned)n);
+    if (lane == 63) s_wsum[wave] = incl;
+    __syncthreads();
+    pos = incl - n;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) {
+      const int x = s_wsum[w];
+      if (w < wave) pos += x;
+      total += x;
+    }
+  }
+  const int blocks = (total + 15) / 16, q = (blocks + a.n_rt - 1) / a.n_rt;
+  const int r0 = grp * q * 16, nrow = min(q * 16, total - r0);
+  if (nrow <= 0) return;  // uniform
+  const int nblk = (nrow + 15) / 16;
+  if (!DENSE) {
+    for (int b = b0; b < b1; ++b) {
+      const int nb = a.t < a.len[b] ? a.nctx[b] : 0;
+      for (int j = max(0, r0 - pos); j < nb && pos + j < r0 + nrow; ++j) list[pos + j - r0] = b * a.Nc + j;
+      pos += nb;
+    }
+    __syncthreads();
+  }
+  // row i of the group (past its last: the last, whose results are dropped)
+  auto row_of = [&](int i) {
+    const int k = min(i, nrow - 1);
+    return DENSE ? r0 + k : list[k];
+  };
+  const uint4* __restrict__ hsrc = reinterpret_cast<const uint4*>(a.h);
+  uint4 hv[U];
+  auto request = [&](int blk) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int c = tid + u * NT;
+      hv[u] = hsrc[(size_t)row_of(16 * blk + c / CPR) * CPR + (c % CPR)];
+    }
+  };
+  auto stage = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int c = tid + u * NT;
+      stage_chunk<BF16>(smem + buf * BUF + (c / CPR) * STRIDE, c % CPR, hv[u]);
+    }
+  };
+  request(0);
+  stage(0);
+  lds_only_barrier();
+  for (int blk = 0; blk < nblk; ++blk) {
+    const int buf = blk & 1;
+    if (blk + 1 < nblk) request(blk + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 acc[NB][NC];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) acc[nb][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const unsigned char* hb = smem + buf * BUF + lr * STRIDE + lg * (BF16 ? 16 : 32);
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+      if constexpr (BF16) {
+        const uint4 h = *reinterpret_cast<const uint4*>(hb + 64 * s);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+          acc[nb][s & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(h), as_bf16x8(wb[nb][s]),
+                                                                   acc[nb][s & 1], 0, 0, 0);
+      } else {
+        const f16x8 ah = as_f16x8(*reinterpret_cast<const uint4*>(hb + 128 * s));
+        const f16x8 al = as_f16x8(*reinterpret_cast<const uint4*>(hb + 128 * s + 16));
+        const f16x8 bh = as_f16x8(wb[0][s]), bl = as_f16x8(wl[s]);
+        f32x4* c = acc[0] + 3 * (s & 1);
+        c[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh, c[0], 0, 0, 0);
+        c[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bl, c[1], 0, 0, 0);
+        c[2] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, bh, c[2], 0, 0, 0);
+      }
+    }
+    if (blk + 1 < nblk) stage(buf ^ 1);
+    // epilogue: the 16 lanes of a DPP row share row 4 lg + i of the block
+    float zr[NB][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float mx = -INFINITY;
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        float zs;
+        if constexpr (BF16)
+          zs = acc[nb][0][i] + acc[nb][1][i];
+        else
+          zs = (((acc[nb][1][i] + acc[nb][2][i]) + (acc[nb][4][i] + acc[nb][5][i])) +
+                (acc[nb][0][i] + acc[nb][3][i])) * zscale;
+        zr[nb][i] = cvalid[nb] ? zs + bias[nb] : -INFINITY;
+        mx = fmaxf(mx, zr[nb][i]);
+      }
+      const float M = row16_max(mx);
+      float e = 0.f;
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+        e += cvalid[nb] ? __builtin_amdgcn_exp2f((zr[nb][i] - M) * kLog2e) : 0.f;
+      const float S = row16_sum(e);
+      if (lr == 0) {
+        s_m[buf][wave][4 * lg + i] = M;
+        s_s[buf][wave][4 * lg + i] = S;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool act = 16 * blk + 4 * lg + i < nrow;
+      const int row = row_of(16 * blk + 4 * lg + i);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const int col = col0 + 16 * nb;
+        const float z = zr[nb][i];
+        if (!TOPK) {
+          if (act && cvalid[nb]) a.logits[(size_t)row * (nvt * kJoinerBN) + col] = z;
+        } else if (col - lr < nvt * kJoinerBN) {
+          // the best KT labels of this 16-column sub-tile (DPP row reductions)
+          unsigned long long key = (cvalid[nb] && col >= 1)
+                                       ? ((unsigned long long)f2ord(z) << 32) | (0xffffffffu - (unsigned)col)
+                                       : 0ull;
+          const size_t ob = ((size_t)row * (nvt * (kJoinerBN / 16)) + (col - lr) / 16) * a.KT;
+          for (int k = 0; k < a.KT; ++k) {
+            const unsigned long long best = row16_max_u64(key);
+            if (act && best != 0ull && key == best) {
+              a.tk_z[ob + k] = z;
+              a.tk_c[ob + k] = col;
+            }
+            if (act && best == 0ull && lr == 0) {
+              a.tk_z[ob + k] = -INFINITY;
+              a.tk_c[ob + k] = -1;
+            }
+            if (key == best) key = 0ull;
+          }
+          if (act && col == 0) a.z0[row] = z;
+        }
+      }
+    }
+    lds_only_barrier();
+    // each vocabulary tile's (max, sum exp) per row, from its waves' parts
+    if (tid < 16 * NVT) {
+      constexpr int WPT = 8 / NVT;  // waves per vocabulary tile
+      const int vt = tid >> 4, r = tid & 15;
+      if (16 * blk + r < nrow && ct * NVT + vt < nvt) {
+        float M = -INFINITY, S = 0.f;
+#pragma unroll
+        for (int w = 0; w < WPT; ++w) M = fmaxf(M, s_m[buf][vt * WPT + w][r]);
+#pragma unroll
+        for (int w = 0; w < WPT; ++w) {
+          const float x = s_s[buf][vt * WPT + w][r];
+          S += x == 0.f ? 0.f : x * expf(s_m[buf][vt * WPT + w][r] - M);
+        }
+        a.stats[(size_t)row_of(16 * blk + r) * nvt + ct * NVT + vt] = make_float2(M, S);
+      }
+    }
+  }
 }
 
 __global__ void k_logp_rows(const float* __restrict__ logits, const float2* __restrict__ stats,
@@ -1041,7 +1409,7 @@ __global__ __launch_bounds__(256) void k_init(ModelDev m, DecodeDev d, GraphDev 
   if (d.len[b] > 0) {
     const int2 zero_off = make_int2(0, 0);  // context (blank, blank)
     const size_t esz = m.bf16 ? 2 : 4;
-    write_h_rows<256>(m, d.enc + (size_t)b * d.T * m.C, 0, &zero_off, 1,
+    write_h_rows<256, true>(m, d.enc + (size_t)b * d.T * m.C, 0, &zero_off, 1,
                       reinterpret_cast<char*>(d.h) + (size_t)b * d.Nc * m.Kpad * esz, m.Kpad, tid);
   }
 }
@@ -1083,7 +1451,7 @@ __global__ __launch_bounds__(256) void k_resume(ModelDev m, DecodeDev d, GraphDe
   }
   __syncthreads();
   const size_t esz = m.bf16 ? 2 : 4;
-  write_h_rows<256>(m, d.enc + (size_t)b * d.T * m.C, 0, s_off, nc,
+  write_h_rows<256, true>(m, d.enc + (size_t)b * d.T * m.C, 0, s_off, nc,
                     reinterpret_cast<char*>(d.h) + (size_t)b * d.Nc * m.Kpad * esz, m.Kpad, tid);
 }
 
@@ -2337,7 +2705,7 @@ __device__ __forceinline__ void search_frame(const ModelDev& m, const GraphDev& 
         dn4[e] = dv;
       }
     } else if (FUSED) {
-      write_h_rows<kSearchThreads>(m, s.enc_next, 0, s.n_rowoff, nC, hl, hstride, tid);
+      write_h_rows<kSearchThreads, false>(m, s.enc_next, 0, s.n_rowoff, nC, hl, hstride, tid);
     } else {
       // (the gathers of up to 16 rows of K = 512 in one batch)
       const size_t esz = m.bf16 ? 2 : 4;
@@ -2354,7 +2722,7 @@ __device__ __forceinline__ void search_frame(const ModelDev& m, const GraphDev& 
       else if ((m.C & 1) == 0)
         write_h_rows_pairs<kSearchThreads, 16>(m, s.enc_next, s.n_rowoff, nC, hrows, m.Kpad, tid);
       else
-        write_h_rows<kSearchThreads, 32>(m, s.enc_next, 0, s.n_rowoff, nC, hrows, m.Kpad, tid);
+        write_h_rows<kSearchThreads, true, 32>(m, s.enc_next, 0, s.n_rowoff, nC, hrows, m.Kpad, tid);
     }
   }
   if (my_keep2) {
@@ -2612,7 +2980,7 @@ __global__ __launch_bounds__(kSearchThreads) void k_stream(ModelDev m, GraphDev 
     for (int i = tid; i < words; i += blockDim.x) reinterpret_cast<int*>(hl)[i] = 0;
   }
   __syncthreads();
-  write_h_rows<kSearchThreads>(m, s.enc_next, 0, s.n_rowoff, s.nc, hl, hstride, tid);
+  write_h_rows<kSearchThreads, false>(m, s.enc_next, 0, s.n_rowoff, s.nc, hl, hstride, tid);
   // staged decoder rows (trivial graph, max_states = 4): those of the initial contexts
   float* dspec = (TRIV && doff) ? reinterpret_cast<float*>(smem + doff) : nullptr;
   if (dspec)
@@ -2899,7 +3267,7 @@ __global__ __launch_bounds__(kSearchThreads) void k_stream_group(ModelDev m, Gra
     for (int i = tid; i < words; i += blockDim.x) reinterpret_cast<int*>(hl)[i] = 0;
   }
   __syncthreads();
-  write_h_rows<kSearchThreads>(m, s.enc_next, 0, s.n_rowoff, s.nc, hl, hstride, tid);
+  write_h_rows<kSearchThreads, false>(m, s.enc_next, 0, s.n_rowoff, s.nc, hl, hstride, tid);
   __syncthreads();
   // FAST: this lane's two columns, the decoder rows of the current contexts there,
   // the survivor buffer and the tuple / context counts of the current frame
@@ -3404,54 +3772,60 @@ hipError_t launch_joiner_t(const ModelDev& m, const JoinArgs& a, const JoinerPla
   return hipGetLastError();
 }
 
-template <bool BF16, int MB, bool TOPK>
-hipError_t launch_joiner_small_t(const ModelDev& m, const JoinArgs& a, const JoinerPlan& p,
-                                 hipStream_t st) {
+template <bool BF16, bool TOPK>
+hipError_t launch_joiner_small(const ModelDev& m, const JoinArgs& a, const JoinerPlan& p,
+                               hipStream_t st) {
   static size_t attr = 0;
   if (p.lds > 65536 && p.lds > attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_joiner_small<BF16, MB, TOPK>,
+    hipError_t e = hipFuncSetAttribute((const void*)k_joiner_small<BF16, TOPK>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
     if (e != hipSuccess) return e;
     attr = p.lds;
   }
-  launch_k((k_joiner_small<BF16, MB, TOPK>), dim3(p.grid), dim3(256), p.lds, st, m, a);
+  launch_k((k_joiner_small<BF16, TOPK>), dim3(p.grid), dim3(256), p.lds, st, m, a);
   return hipGetLastError();
 }
 
-template <bool BF16, bool TOPK>
-hipError_t launch_joiner_small(const ModelDev& m, const JoinArgs& a, const JoinerPlan& p,
+template <bool BF16, bool TOPK, bool DENSE>
+hipError_t launch_joiner_sweep(const ModelDev& m, const JoinArgs& a, const JoinerPlan& p,
                                hipStream_t st) {
-  switch (p.MB) {
-    case 1: return launch_joiner_small_t<BF16, 1, TOPK>(m, a, p, st);
-    case 2: return launch_joiner_small_t<BF16, 2, TOPK>(m, a, p, st);
-    default: return launch_joiner_small_t<BF16, 4, TOPK>(m, a, p, st);
+  if (p.lds > 65536) {
+    hipError_t e = hipFuncSetAttribute((const void*)k_joiner_sweep<BF16, TOPK, DENSE>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
+    if (e != hipSuccess) return e;
   }
+  launch_k((k_joiner_sweep<BF16, TOPK, DENSE>), dim3(p.grid), dim3(kSweepThreads), p.lds, st, m, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_joiner(const ModelDev& m, const JoinArgs& a, const JoinerPlan& p, bool topk,
                          hipStream_t st) {
-  if (p.MB == 0) {  // the GEMM tiles address h and W with 32-bit byte offsets
+  if (p.sweep) {
+    if (m.Kpad != kSweepK || (topk && a.rows_mode)) return hipErrorInvalidValue;
+    if (a.rows_mode)
+      return m.bf16 ? launch_joiner_sweep<true, false, true>(m, a, p, st)
+                    : launch_joiner_sweep<false, false, true>(m, a, p, st);
+    if (m.bf16)
+      return topk ? launch_joiner_sweep<true, true, false>(m, a, p, st)
+                  : launch_joiner_sweep<true, false, false>(m, a, p, st);
+    return topk ? launch_joiner_sweep<false, true, false>(m, a, p, st)
+                : launch_joiner_sweep<false, false, false>(m, a, p, st);
+  }
+  if (!p.small) {  // the GEMM tiles address h and W with 32-bit byte offsets
     const unsigned long long rowb = (unsigned long long)m.Kpad * (m.bf16 ? 2 : 4);
     if ((unsigned long long)a.R * rowb >= (1ull << 32) || (unsigned long long)m.Vpad * rowb >= (1ull << 32))
       return hipErrorInvalidValue;
   }
-  if (p.MB == 0 && p.shape == 1) {  // bf16 logits only
+  if (!p.small && p.shape == 1) {  // bf16 logits only
     if (!m.bf16 || topk) return hipErrorInvalidValue;
     return launch_joiner_t<true, false, 4, 8>(m, a, p, st);
   }
-  if (p.MB == 0 && p.shape == 2) {
+  if (!p.small) {
     if (m.bf16)
       return topk ? launch_joiner_t<true, true, 2, 2>(m, a, p, st)
                   : launch_joiner_t<true, false, 2, 2>(m, a, p, st);
     return topk ? launch_joiner_t<false, true, 2, 2>(m, a, p, st)
                 : launch_joiner_t<false, false, 2, 2>(m, a, p, st);
-  }
-  if (p.MB == 0) {
-    if (m.bf16)
-      return topk ? launch_joiner_t<true, true, 2, 4>(m, a, p, st)
-                  : launch_joiner_t<true, false, 2, 4>(m, a, p, st);
-    return topk ? launch_joiner_t<false, true, 2, 4>(m, a, p, st)
-                : launch_joiner_t<false, false, 2, 4>(m, a, p, st);
   }
   if (m.bf16)
     return topk ? launch_joiner_small<true, true>(m, a, p, st) : launch_joiner_small<true, false>(m, a, p, st);
@@ -3478,6 +3852,7 @@ bool take_launch_events(hipEvent_t* start, hipEvent_t* stop) {
 JoinerPlan plan_joiner(int rows, int Vpad, int Kpad, int bf16, int ncu, bool topk) {
   JoinerPlan p;
   p.shape = 0;
+  p.small = p.sweep = false;
   const int esz = bf16 ? 2 : 4;
   const int nvt = Vpad / kJoinerBN;
   // bf16 logits: 256 x 256 GEMM tiles when they give every compute unit several
@@ -3486,55 +3861,65 @@ JoinerPlan plan_joiner(int rows, int Vpad, int Kpad, int bf16, int ncu, bool top
     p.n_ct = (nvt * kJoinerBN + kJWideBN - 1) / kJWideBN;
     const long long tiles = (long long)p.n_rt * p.n_ct;
     if (tiles >= 4LL * ncu) {
-      p.MB = 0;
       p.shape = 1;
       p.grid = (int)(8 * ((tiles + 7) / 8));
       p.lds = kJWideLds;
       return p;
     }
   }
-  // 128 x 128 GEMM tiles when they give every compute unit one (MB = 0)
-  p.n_rt = (rows + kJBM - 1) / kJBM;
+  // 64 x 128 GEMM tiles when there are at least two per compute unit (the count below is of
+  // 128 x 128): they read each operand less often than the sweep.  (Joiner alone, fp32,
+  // C = 512, MI355X: V = 1,300, 2,048 rows 37.7 us against 41.3, 6,000 rows 77.7 against
+  // 87.1.  They already lead by a little at one per compute unit, but their error, 9e-8,
+  // is above the 7e-8 of the other two.)
+  p.n_rt = (rows + 127) / 128;
   p.n_ct = (nvt + 1) / 2;
   if ((long long)p.n_rt * p.n_ct >= ncu) {
-    p.MB = 0;
-    if ((long long)p.n_rt * p.n_ct < 4LL * ncu) {
-      // a few 128 x 128 tiles per CU: 64 x 128 tiles (three workgroups per CU), which
-      // spread the work over the CUs in finer and more even parts
-      p.shape = 2;
-      p.n_rt = (rows + kJHalfBM - 1) / kJHalfBM;
-      p.lds = kJHalfLds;
-    } else {
-      p.lds = kJLds;
-    }
-    p.grid = 8 * ((p.n_ct + 7) / 8) * p.n_rt;
+    p.n_rt = (rows + kJHalfBM - 1) / kJHalfBM;
+    p.lds = kJHalfLds;
+    p.grid = joiner_grid(p.n_rt, p.n_ct);
     return p;
   }
-  // Otherwise small tiles: the largest row block (4 or 2 MFMA blocks, else 1) whose h
-  // tile leaves room for two workgroups per CU and still yields a workgroup per CU.
-  int MB = 1;
-  for (int cand : {4, 2}) {
-    const size_t lds = (size_t)16 * cand * (Kpad + (bf16 ? 8 : 4)) * esz;
-    const long long tiles = (long long)((rows + 16 * cand - 1) / (16 * cand)) * nvt;
-    if (lds <= 78 * 1024 && tiles >= ncu) {
-      MB = cand;
-      break;
+  // The sweep from one 16 x 64 tile per compute unit (C <= 512): V = 500, 512 rows 16.1 us
+  // against 17.4 with small tiles, 6,000 rows 49 against 66; fewer (V = 1,300, 64 rows:
+  // 84 tiles) are even, and fewer still leave compute units without a workgroup of its
+  // eight waves.
+  p.n_rt = (rows + 15) / 16;
+  p.n_ct = nvt;
+  if (Kpad == kSweepK && (long long)p.n_rt * p.n_ct >= ncu) {
+    const int cols = bf16 ? kSweepCols<true> : kSweepCols<false>;
+    const int n_ct = (Vpad + cols - 1) / cols, blocks = p.n_rt;
+    const int groups = std::max(1, std::min(blocks, ncu / n_ct)), share = (blocks + groups - 1) / groups;
+    if (16 * share <= kSweepMaxRows) {
+      p.sweep = true;
+      p.n_rt = groups;
+      p.n_ct = n_ct;
+      p.grid = groups * n_ct;
+      p.lds = 2 * 16 * (size_t)(bf16 ? kSweepStride<true> : kSweepStride<false>) + (size_t)share * 16 * sizeof(int);
+      return p;
     }
   }
-  p.MB = MB;
-  p.n_rt = (rows + 16 * MB - 1) / (16 * MB);
-  p.n_ct = nvt;
-  p.grid = 8 * ((nvt + 7) / 8) * p.n_rt;
-  p.lds = (size_t)16 * MB * (Kpad + (bf16 ? 8 : 4)) * esz;
+  p.small = true;
+  p.grid = joiner_grid(p.n_rt, p.n_ct);
+  p.lds = (size_t)16 * (Kpad + (bf16 ? 8 : 4)) * esz;
   return p;
 }
 
 hipError_t launch_model_setup(const float* embed, const float* conv, const float* w_out,
                               const float* b_out, int V, int C, int Kpad, int Vpad, int bf16,
-                              float* P0, float* P1, float* Wf, uint16_t* Wb, void* Wi,
-                              float* bias, hipStream_t st) {
+                              float* P0, float* P1, uint16_t* Ws, uint16_t* Wsi, float* zscale,
+                              uint16_t* Wb, void* Wi, float* bias, hipStream_t st) {
+  if (!bf16) {
+    hipError_t e = launch_fill_i32(reinterpret_cast<int*>(zscale), 2, 0, st);
+    if (e != hipSuccess) return e;
+    const long long n = (long long)V * C;
+    hipLaunchKernelGGL(k_weight_max, dim3(grid_for(n, 2048, 512)), dim3(256), 0, st, w_out, n,
+                       reinterpret_cast<unsigned*>(zscale) + 1);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(k_model_setup, dim3(grid_for((long long)Vpad * Kpad, 256)), dim3(256), 0, st,
-                     embed, conv, w_out, b_out, V, C, Kpad, Vpad, bf16, P0, P1, Wf, Wb, Wi, bias);
+                     embed, conv, w_out, b_out, V, C, Kpad, Vpad, bf16, P0, P1, Ws, Wsi, zscale, Wb,
+                     Wi, bias);
   return hipGetLastError();
 }
 
@@ -3580,6 +3965,7 @@ hipError_t launch_joiner_frame(const ModelDev& m, const DecodeDev& d, const Join
   a.len = d.len;
   a.nctx = d.nctx;
   a.t = t;
+  a.B = d.B;
   a.Nc = d.Nc;
   return launch_joiner(m, a, p, d.KT > 0, st);
 }

@@ -81,3 +81,61 @@ def test_joiner_large_batches_sampled_rows(V, C, sigma, R, dtype):
     say(f"  max |dlogp| over {len(idx)} rows = {err:.3g}")
     assert err <= (1e-4 if dtype == "fp32" else 2e-2)
     assert np.isfinite(got).all()
+
+
+# Edges of the joiner's tilings: sweep (C <= 512, at least one 16 x 64 tile per compute unit;
+# 128 or 256 columns a workgroup, groups of 16-row blocks), GEMM tiles with few and with
+# ragged column tiles, small tiles with K beyond one chunk.
+TILES = [  # (V, C, R)
+    (500, 512, 600), (60, 512, 4200), (64, 500, 4097), (65, 33, 2113), (129, 512, 1366),
+    (513, 511, 500), (2, 8, 4100), (1000, 512, 256), (5000, 512, 300),
+    (200, 512, 16390), (641, 512, 6145),
+    (1000, 768, 1000), (300, 1025, 130), (2000, 640, 2100),
+]
+
+
+@pytest.mark.parametrize("V,C,R", TILES)
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_joiner_tilings(V, C, R, dtype):
+    import torch
+    from paper_2211_00484_amd import tbs
+    say(f"joiner tiling V={V} C={C} R={R} {dtype}")
+    rng = np.random.default_rng(V * 31 + C + R)
+    model_np = synth.make_model(rng, V, C, 0.1)
+    enc = rng.standard_normal((R, C), dtype=np.float32)
+    a = rng.integers(0, V, R).astype(np.int32)
+    b = rng.integers(0, V, R).astype(np.int32)
+    model = tbs.Model.from_synth(model_np, dtype=dtype)
+    ctx = torch.from_numpy((a.astype(np.int64) * V + b).astype(np.int32))
+    got = tbs.joiner_logp(model, torch.from_numpy(enc).cuda(), ctx).cpu().numpy()
+    idx = np.unique(np.concatenate([np.arange(min(R, 40)), np.arange(max(0, R - 40), R),
+                                    rng.integers(0, R, 200)]))
+    want = oracle.logp(model_np, enc[idx], a[idx], b[idx], bf16=(dtype == "bf16"))
+    # fp32: tanh and products to 2e-7 each over C terms of |w| ~ 0.1; bf16: a tanh that
+    # rounds to its neighbour (2^-9) now and then
+    assert np.abs(got[idx] - want).max() <= (2e-5 if dtype == "fp32" else 2e-2)
+    assert np.isfinite(got).all()
+
+
+@pytest.mark.parametrize("scale", [0.0, 1e-37, 1e-12, 1.0, 1e6, 1e30])
+@pytest.mark.parametrize("V,C,R", [(100, 64, 50), (100, 64, 2600), (700, 64, 3000), (300, 600, 40)])
+def test_joiner_weight_scales(scale, V, C, R):
+    """fp32 weights of any magnitude, rows 2^0 ... 2^-30 below the largest: the logits keep
+    fp32's accuracy relative to their products (bias 0, so log-probabilities show them)."""
+    import torch
+    from paper_2211_00484_amd import tbs
+    rng = np.random.default_rng(3)
+    m = synth.make_model(rng, V, C, 1.0)
+    m.w_out *= (np.float32(scale) * 2.0 ** -rng.integers(0, 31, size=(V, 1))).astype(np.float32)
+    m.b_out[:] = 0
+    enc = rng.standard_normal((R, C), dtype=np.float32)
+    a, b = rng.integers(0, V, R), rng.integers(0, V, R)
+    model = tbs.Model.from_synth(m)
+    got = tbs.joiner_logp(model, torch.from_numpy(enc).cuda(),
+                          torch.from_numpy((a * V + b).astype(np.int32))).cpu().numpy()
+    dec = np.maximum(m.conv[:, 0] * m.embed[a].astype(np.float64) + m.conv[:, 1] * m.embed[b], 0)
+    z = np.tanh(enc + dec) @ m.w_out.astype(np.float64).T
+    want = z - (z.max(1, keepdims=True) + np.log(np.exp(z - z.max(1, keepdims=True)).sum(1, keepdims=True)))
+    # tanh to 2e-7 absolute, products to 2^-22, sums of C terms of the largest weights
+    tol = 1e-6 + 1e-6 * np.sqrt(C) * np.abs(m.w_out).max() + 2e-7 * np.abs(want)
+    assert (np.abs(got - want) <= tol).all()
