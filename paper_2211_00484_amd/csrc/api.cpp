@@ -110,8 +110,6 @@ struct HypWork {
   int* ctx[2] = {nullptr, nullptr};
   double* score[2] = {nullptr, nullptr};
   int* nh[2] = {nullptr, nullptr};
-  int* rowctx = nullptr;
-  int* hrow = nullptr;
   int* hist = nullptr;
   void* h = nullptr;
   float* logits = nullptr;
@@ -130,8 +128,6 @@ struct HypWork {
       (void)hipFree(nh[i]);
     }
     (void)hipFree(len);
-    (void)hipFree(rowctx);
-    (void)hipFree(hrow);
     (void)hipFree(hist);
     (void)hipFree(h);
     (void)hipFree(logits);
@@ -1787,8 +1783,6 @@ tbs_status tbs_hyp_search(const tbs_model* model, const tbs_hyp_params* params,
       if (e == hipSuccess) e = dalloc(&w.nh[i], (size_t)B);
     }
     if (e == hipSuccess) e = dalloc(&w.len, (size_t)B);
-    if (e == hipSuccess) e = dalloc(&w.rowctx, BN);
-    if (e == hipSuccess) e = dalloc(&w.hrow, BN);
     if (e == hipSuccess) e = dalloc(&w.hist, (size_t)T * BN);
     if (e == hipSuccess) e = dalloc((char**)&w.h, BN * m->Kpad * (m->bf16 ? 2 : 4));
     if (e == hipSuccess) e = dalloc(&w.logits, BN * m->Vpad);
@@ -1820,8 +1814,6 @@ tbs_status tbs_hyp_search(const tbs_model* model, const tbs_hyp_params* params,
     d.score[i] = w.score[i];
     d.nh[i] = w.nh[i];
   }
-  d.rowctx = w.rowctx;
-  d.hrow = w.hrow;
   d.hist = w.hist;
   d.enc = encoder_out;
   d.h = w.h;

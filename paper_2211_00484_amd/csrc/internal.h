@@ -268,15 +268,13 @@ struct HypDev {
   int B, T, N, merge_logadd;
   const int* len;                     // [B]
   const float* enc;                   // [B][T][C] encoder output
-  void* h;                            // [B*N][Kpad] joiner rows of the next frame
+  void* h;                            // [B*N][Kpad] joiner rows of the next frame, one per hypothesis
   unsigned long long* hash[2];        // [B][N] per frame parity: hash of the sequence
   unsigned long long* phash[2];       // hash of the sequence without its last label
   int* n[2];                          // sequence length
   int* ctx[2];                        // last two labels a * V + b
   double* score[2];
   int* nh[2];                         // [B] hypotheses
-  int* rowctx;                        // [B*N] joiner row contexts (-1: none)
-  int* hrow;                          // [B*N] joiner row of each hypothesis
   int* hist;                          // [T][B][N] parent << 16 | label
 };
 hipError_t launch_hyp_init(const ModelDev& m, const HypDev& d, hipStream_t st);

@@ -72,6 +72,18 @@ def test_beam_sizes(N, merge):
     assert _run(inputs, model, N, merge) >= 1
 
 
+# The step's variants: scores cached by four or by sixteen waves, rescored; columns at the
+# edges of a wave's share; C not a multiple of 4.
+@pytest.mark.parametrize("V,N,C", [(255, 8, 33), (257, 8, 16), (400, 16, 100), (3000, 3, 34),
+                                   (1025, 7, 64), (5000, 8, 64)])
+@pytest.mark.parametrize("merge", ["max", "logadd"])
+def test_step_variants(V, N, C, merge):
+    rng = np.random.default_rng(V + N)
+    model = synth.make_model(rng, V, C, 0.6)
+    inputs = synth.make_inputs(rng, 3, 14, C, length_range=(5, 14))
+    _run(inputs, model, N, merge)
+
+
 def test_ragged_and_empty_streams():
     rng = np.random.default_rng(9)
     model = synth.make_model(rng, 16, 32, 0.3)
