@@ -483,49 +483,55 @@ __device__ void write_h_rows_pairs(const ModelDev& m, const float* __restrict__ 
   }
 }
 
-// h rows for explicit (encoder row, context) pairs: one workgroup per row.
-__global__ __launch_bounds__(256) void k_h_rows(ModelDev m, const float* __restrict__ enc_rows,
-                                                const int* __restrict__ ctx, void* __restrict__ h) {
-  __shared__ int2 off;
-  const int r = blockIdx.x;
-  if (threadIdx.x == 0) {
-    const int c = ctx[r], a = c / m.V;
-    off = make_int2(a * m.Kpad, (c - a * m.V) * m.Kpad);
-  }
-  __syncthreads();
-  const size_t esz = m.bf16 ? 2 : 4;
-  write_h_rows<256, true>(m, enc_rows + (size_t)r * m.C, 0, &off, 1,
-                    reinterpret_cast<char*>(h) + (size_t)r * m.Kpad * esz, m.Kpad, threadIdx.x);
-}
-
 // Rows of a dense (encoder row, context) table: batch row r is table row row0 + r,
 // with context ctx[row0 + r] (-1: an empty slot, written as zeros) and encoder row
-// enc + ((row0 + r) / per_enc) * enc_stride.
-__global__ __launch_bounds__(256) void k_h_rows_dense(ModelDev m, const float* __restrict__ enc,
-                                                      const int* __restrict__ ctx, long long row0,
-                                                      int per_enc, long long enc_stride,
-                                                      void* __restrict__ h) {
-  __shared__ int2 off;
-  const long long g = row0 + blockIdx.x;
-  const int c = ctx[g];
-  const size_t esz = m.bf16 ? 2 : 4;
-  char* hrow = reinterpret_cast<char*>(h) + (size_t)blockIdx.x * m.Kpad * esz;
-  if (c < 0) {
-    for (int k = threadIdx.x; k < m.Kpad; k += blockDim.x) {
-      if (m.bf16)
-        reinterpret_cast<uint16_t*>(hrow)[k] = 0;
-      else
-        reinterpret_cast<float*>(hrow)[k] = 0.f;
+// enc + ((row0 + r) / per_enc) * enc_stride.  One wave per row, a column quad per lane and
+// step, the steps' loads in flight together (bound: the writes of h).  (32,000 rows, C = 512:
+// 46 us with a workgroup and a barrier per row.)
+__global__ __launch_bounds__(256) void k_h_rows(ModelDev m, const float* __restrict__ enc,
+                                                const int* __restrict__ ctx, long long row0,
+                                                int per_enc, long long enc_stride, int R,
+                                                void* __restrict__ h) {
+  const int lane = threadIdx.x & 63, r = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= R) return;  // whole wave
+  const long long g = row0 + r;
+  const int c = ctx[g], C = m.C, Kpad = m.Kpad;
+  const bool quads = (C & 3) == 0 && (enc_stride & 3) == 0;
+  const bool aligned = quads && (reinterpret_cast<uintptr_t>(enc) & 15) == 0;
+  const float* e = enc + (size_t)(g / per_enc) * enc_stride;
+  const int a = max(c, 0) / m.V, b = max(c, 0) - a * m.V;
+  const float* P0 = m.P0 + (size_t)a * Kpad;
+  const float* P1 = m.P1 + (size_t)b * Kpad;
+#pragma unroll 2
+  for (int k = 4 * lane; k < Kpad; k += 256) {
+    const float4 p0 = *reinterpret_cast<const float4*>(P0 + k);
+    const float4 p1 = *reinterpret_cast<const float4*>(P1 + k);
+    float4 x;
+    if (aligned) {
+      x = *reinterpret_cast<const float4*>(e + min(k, C - 4));
+    } else {
+      x.x = e[min(k, C - 1)];
+      x.y = e[min(k + 1, C - 1)];
+      x.z = e[min(k + 2, C - 1)];
+      x.w = e[min(k + 3, C - 1)];
     }
-    return;
+    auto at = [&](int j, float ev, float q0, float q1) {
+      return c >= 0 && k + j < C ? tanh_fast(ev + fmaxf(q0 + q1, 0.f)) : 0.f;
+    };
+    const float h0 = at(0, x.x, p0.x, p1.x), h1 = at(1, x.y, p0.y, p1.y);
+    const float h2 = at(2, x.z, p0.z, p1.z), h3 = at(3, x.w, p0.w, p1.w);
+    const size_t o = (size_t)r * Kpad + k;
+    if (m.bf16) {
+      *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(h) + o) =
+          make_uint2((unsigned)f32_to_bf16_rne(h0) | ((unsigned)f32_to_bf16_rne(h1) << 16),
+                     (unsigned)f32_to_bf16_rne(h2) | ((unsigned)f32_to_bf16_rne(h3) << 16));
+    } else {
+      uint4 v;
+      split_pair(h0, h1, v.x, v.z);
+      split_pair(h2, h3, v.y, v.w);
+      *reinterpret_cast<uint4*>(reinterpret_cast<unsigned*>(h) + o) = v;
+    }
   }
-  if (threadIdx.x == 0) {
-    const int a = c / m.V;
-    off = make_int2(a * m.Kpad, (c - a * m.V) * m.Kpad);
-  }
-  __syncthreads();
-  write_h_rows<256, true>(m, enc + (size_t)(g / per_enc) * enc_stride, 0, &off, 1, hrow, m.Kpad,
-                    threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1362,22 +1368,24 @@ __global__ __launch_bounds__(kSweepThreads) void k_joiner_sweep(ModelDev m, Join
   }
 }
 
-__global__ void k_logp_rows(const float* __restrict__ logits, const float2* __restrict__ stats,
-                            int nvt, int V, int Vpad, float* __restrict__ out) {
-  const int r = blockIdx.x;
-  __shared__ double s_lse;
-  if (threadIdx.x == 0) {
-    const float2* st = stats + (size_t)r * nvt;
-    float M = -INFINITY;
-    for (int i = 0; i < nvt; ++i) M = fmaxf(M, st[i].x);
-    float S = 0.f;
-    for (int i = 0; i < nvt; ++i) S += st[i].y == 0.f ? 0.f : st[i].y * expf(st[i].x - M);
-    s_lse = lse_of(M, S);
-  }
-  __syncthreads();
-  const double l = s_lse;
-  for (int v = threadIdx.x; v < V; v += blockDim.x)
-    out[(size_t)r * V + v] = logp_of(logits[(size_t)r * Vpad + v], l);
+// Log-probabilities of the rows' logits, WPR waves per row (each takes the row's normaliser
+// for itself: no barrier); one for narrow rows, so that a wave has a row's worth of work.
+template <int WPR>
+__global__ __launch_bounds__(256) void k_logp_rows(const float* __restrict__ logits,
+                                                   const float2* __restrict__ stats, int nvt,
+                                                   int V, int Vpad, int R, float* __restrict__ out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = blockIdx.x * (4 / WPR) + wave / WPR;
+  if (r >= R) return;  // whole wave
+  const float2* st = stats + (size_t)r * nvt;
+  float M = -INFINITY, S = 0.f;
+  for (int i = lane; i < nvt; i += 64) M = fmaxf(M, st[i].x);
+  M = wave_max_f(M);
+  for (int i = lane; i < nvt; i += 64) S += st[i].y == 0.f ? 0.f : st[i].y * expf(st[i].x - M);
+  const double l = lse_of(M, wave_sum_f(S));
+  const float* z = logits + (size_t)r * Vpad;
+#pragma unroll 8
+  for (int v = (wave % WPR) * 64 + lane; v < V; v += 64 * WPR) out[(size_t)r * V + v] = logp_of(z[v], l);
 }
 
 // ---------------------------------------------------------------------------
@@ -4147,8 +4155,8 @@ hipError_t launch_h_rows_dense(const ModelDev& m, const float* enc, long long en
                                const int* ctx, long long row0, int per_enc, int R, void* h,
                                hipStream_t st) {
   if (R <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_h_rows_dense, dim3(R), dim3(256), 0, st, m, enc, ctx, row0, per_enc,
-                     enc_stride, h);
+  hipLaunchKernelGGL(k_h_rows, dim3((R + 3) / 4), dim3(256), 0, st, m, enc, ctx, row0, per_enc,
+                     enc_stride, R, h);
   return hipGetLastError();
 }
 
@@ -4180,23 +4188,15 @@ hipError_t launch_joiner_gemm(const ModelDev& m, const void* h, int R, float* lo
 hipError_t launch_joiner_rows(const ModelDev& m, const float* enc_rows, const int* ctx, int R,
                               void* h, float* logits, float2* stats, float* out_logp, int ncu,
                               hipStream_t st) {
-  hipLaunchKernelGGL(k_h_rows, dim3(R), dim3(256), 0, st, m, enc_rows, ctx, h);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_joiner_dense(m, enc_rows, m.C, ctx, 0, 1, R, h, logits, stats, ncu, st);
   if (e != hipSuccess) return e;
-  const JoinerPlan p = plan_joiner(R, m.Vpad, m.Kpad, m.bf16, ncu);
-  JoinArgs a{};
-  a.h = h;
-  a.logits = logits;
-  a.stats = stats;
-  a.R = R;
-  a.n_rt = p.n_rt;
-  a.n_ct = p.n_ct;
-  a.nvt = m.Vpad / kJoinerBN;
-  a.rows_mode = 1;
-  e = launch_joiner(m, a, p, false, st);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_logp_rows, dim3(R), dim3(256), 0, st, logits, stats, a.nvt, m.V, m.Vpad,
-                     out_logp);
+  const int nvt = m.Vpad / kJoinerBN;
+  if (m.V <= 1024)
+    hipLaunchKernelGGL(k_logp_rows<1>, dim3((R + 3) / 4), dim3(256), 0, st, logits, stats, nvt, m.V,
+                       m.Vpad, R, out_logp);
+  else
+    hipLaunchKernelGGL(k_logp_rows<4>, dim3(R), dim3(256), 0, st, logits, stats, nvt, m.V, m.Vpad,
+                       R, out_logp);
   return hipGetLastError();
 }
 

@@ -281,9 +281,8 @@ constexpr int kStageF = kLT;  // frames per stage at most (one candidate per thr
 
 template <int ACAP, int DCAP, int XCAP>
 struct Stage {
-  int src[ACAP];
-  int lab[ACAP];
-  float w[ACAP];
+  unsigned sl[ACAP];                // source node and label of each arc (pack_arc)
+  float w[XCAP > 0 ? 1 : ACAP];     // arc weights (XCAP = 0)
   int dp[DCAP];                     // [frames][Ns+1]
   double pc[XCAP > 0 ? ACAP : 1];   // arc shares (XCAP > 0)
   int fo[kStageF + 1];              // first arc of each frame, relative to a0
@@ -292,14 +291,20 @@ struct Stage {
   int lo, hi, staged;
 };
 
+// Source node (below 256) and label (below 2^16) of an arc in one word.
+static_assert(kMaxStates <= 256 && kMaxVocab <= 65536, "pack_arc");
+__device__ __forceinline__ unsigned pack_arc(const int4& x) { return (unsigned)x.z << 8 | (unsigned)x.x; }
+__device__ __forceinline__ int arc_src(unsigned a) { return (int)(a & 0xffu); }
+__device__ __forceinline__ int arc_label(unsigned a) { return (int)(a >> 8); }
+
 struct FrameView {
-  const int* dp;   // [Ns+1] offsets of each destination's arcs within the frame
-  const int* src;  // arc k: src[k * stride], lab[k * stride]
-  const int* lab;
-  int stride;
-  const float* w;
-  const double* pc;  // arc shares of the destination's score (XCAP > 0 only)
-  int n1;            // nodes of frame f+1
+  const int* dp;       // [Ns+1] offsets of each destination's arcs within the frame
+  const unsigned* sl;  // staged arcs, or null
+  const int4* arcs;    // the frame's arcs in global memory
+  const float* w;      // weights (XCAP = 0 only)
+  const double* pc;    // arc shares of the destination's score (XCAP > 0 only)
+  int n1;              // nodes of frame f+1
+  __device__ __forceinline__ unsigned arc(int k) const { return sl ? sl[k] : pack_arc(arcs[k]); }
 };
 
 // Stages frames [lo, hi) of stream b: forward from f (lo = f, hi <= fend), or backward
@@ -330,11 +335,11 @@ __device__ void stage_frames(const LatticeDev& L, Stage<ACAP, DCAP, XCAP>& s, in
     const long long a0 = off[lo];
     const int na = (int)(off[hi] - a0);
     for (int i = tid; i < na; i += kLT) {
-      const int4 x = L.arcs[a0 + i];
-      s.src[i] = x.x;
-      s.lab[i] = x.z;
-      s.w[i] = L.w[a0 + i];
-      if (XCAP > 0) s.pc[i] = L.pc[a0 + i];
+      s.sl[i] = pack_arc(L.arcs[a0 + i]);
+      if (XCAP > 0)
+        s.pc[i] = L.pc[a0 + i];
+      else
+        s.w[i] = L.w[a0 + i];
     }
     const int* dsrc = L.dptr + ((size_t)b * T + lo) * (Ns + 1);
     for (int i = tid; i < nfr * (Ns + 1); i += kLT) s.dp[i] = dsrc[i];
@@ -352,19 +357,17 @@ __device__ FrameView frame_view(const LatticeDev& L, const Stage<ACAP, DCAP, XCA
   if (s.staged) {
     const int i = f - s.lo, a = s.fo[i];
     v.dp = s.dp + i * (Ns + 1);
-    v.src = s.src + a;
-    v.lab = s.lab + a;
-    v.stride = 1;
-    v.w = s.w + a;
+    v.sl = s.sl + a;
+    v.arcs = nullptr;
+    v.w = XCAP > 0 ? nullptr : s.w + a;
     v.pc = XCAP > 0 ? s.pc + a : nullptr;
     v.n1 = s.nn1[i];
   } else {
     const size_t fi = (size_t)b * T + f;
     const long long a = L.off[fi];
     v.dp = L.dptr + fi * (Ns + 1);
-    v.src = reinterpret_cast<const int*>(L.arcs + a);
-    v.lab = v.src + 2;
-    v.stride = 4;
+    v.sl = nullptr;
+    v.arcs = L.arcs + a;
     v.w = L.w + a;
     v.pc = L.pc + a;
     v.n1 = L.nn[(size_t)b * (T + 1) + f + 1];
@@ -401,7 +404,7 @@ __global__ __launch_bounds__(kLT) void k_lat_forward(LatticeDev L, GraphDev g0) 
             double e[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i)
-              e[i] = k0 + i < k1 ? s_al[cur][v.src[(k0 + i) * v.stride]] + (double)v.w[k0 + i]
+              e[i] = k0 + i < k1 ? s_al[cur][arc_src(v.arc(k0 + i))] + (double)v.w[k0 + i]
                                  : neg_inf();
 #pragma unroll
             for (int i = 0; i < 8; ++i) x = fmax(x, e[i]);
@@ -422,14 +425,14 @@ __global__ __launch_bounds__(kLT) void k_lat_forward(LatticeDev L, GraphDev g0) 
             }
           } else {
             for (int k = k0; k < k1; ++k)
-              x = fmax(x, s_al[cur][v.src[k * v.stride]] + (double)v.w[k]);
+              x = fmax(x, s_al[cur][arc_src(v.arc(k))] + (double)v.w[k]);
             if (x != neg_inf()) {
               double sum = 0.0;
               for (int k = k0; k < k1; ++k)
-                sum += exp(s_al[cur][v.src[k * v.stride]] + (double)v.w[k] - x);
+                sum += exp(s_al[cur][arc_src(v.arc(k))] + (double)v.w[k] - x);
               x += log(sum);
               for (int k = k0; k < k1; ++k)
-                pc[k] = exp(s_al[cur][v.src[k * v.stride]] + (double)v.w[k] - x);
+                pc[k] = exp(s_al[cur][arc_src(v.arc(k))] + (double)v.w[k] - x);
             }
           }
         }
@@ -560,9 +563,9 @@ __global__ __launch_bounds__(kLT) void k_lat_sample(LatticeDev L, NBestDev N) {
           continue;
         }
         if (pp) pp[f] = a0 + k;
-        const int lab = v.lab[(a0 + k) * v.stride];
-        if (lab > 0) seq[T - 1 - nt++] = lab;  // labels arrive last first
-        node = v.src[(a0 + k) * v.stride];
+        const unsigned arc = v.arc(a0 + k);
+        if (arc_label(arc) > 0) seq[T - 1 - nt++] = arc_label(arc);  // labels arrive last first
+        node = arc_src(arc);
       }
     }
     if (act) {
@@ -653,14 +656,17 @@ __device__ __forceinline__ double wave_max_f64(double x) {
   return x;
 }
 
-// DP buffers: per wave kSeqLds doubles of LDS (small enough for three workgroups per
+// DP buffers: per wave kSeqLds doubles of LDS (small enough for four workgroups per
 // compute unit), used when the sequence's band fits
 // (2 * Ns * band width); otherwise the wave's slice of the global scratch.
 constexpr int kSeqLds = 768;
 
-__global__ __launch_bounds__(kLT) void k_lat_seqscore(LatticeDev L, NBestDev N) {
+// Bound: LDS round trips of a wave's frame, so the waves in flight: at 39 KB and 128
+// registers four workgroups share a compute unit (three before, whose 768 slots took the
+// 800 workgroups of 32 streams x 100 sequences in two rounds).
+__global__ __launch_bounds__(kLT, 4) void k_lat_seqscore(LatticeDev L, NBestDev N) {
   __shared__ Stage<512, 512, 1> s;
-  __shared__ int s_y[kSeqWaves][kYStage];
+  __shared__ uint16_t s_y[kSeqWaves][kYStage];
   __shared__ double s_dp[kSeqWaves][kSeqLds];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int Ns = L.Ns, T = L.T, n = N.n, b = blockIdx.y;
@@ -679,7 +685,7 @@ __global__ __launch_bounds__(kLT) void k_lat_seqscore(LatticeDev L, NBestDev N) 
     const int u = u0 + wv;
     const bool act = u < nu;
     int Ly = 0;
-    const int* y = s_y[wv];
+    const int* yg = nullptr;  // the labels, if not in s_y
     // band width of this sequence: min(|y|, len - |y|) + 1
     int W = 1;
     bool in_lds = true;
@@ -687,11 +693,11 @@ __global__ __launch_bounds__(kLT) void k_lat_seqscore(LatticeDev L, NBestDev N) 
     if (act) {
       const size_t pi = (size_t)b * n + N.first[(size_t)b * n + u];
       Ly = N.ntok[pi];
-      const int* yg = N.seq + pi * T;
+      const int* seq = N.seq + pi * T;
       if (Ly <= kYStage)
-        for (int k = lane; k < Ly; k += 64) s_y[wv][k] = yg[k];
+        for (int k = lane; k < Ly; k += 64) s_y[wv][k] = (uint16_t)seq[k];
       else
-        y = yg;
+        yg = seq;
       W = (Ly < len - Ly ? Ly : len - Ly) + 1;
       in_lds = 2 * nmax * W <= kSeqLds;
       if (!in_lds) A0 = gdp;  // the host allots it whenever a band may not fit
@@ -710,33 +716,36 @@ __global__ __launch_bounds__(kLT) void k_lat_seqscore(LatticeDev L, NBestDev N) 
           const int w1 = hi1 - lo1 + 1;
           const FrameView v = frame_view(L, s, b, f);
           double mx = 0.0;
+          const float inv_w1 = __builtin_amdgcn_rcpf((float)w1);
           for (int q = lane; q < v.n1 * w1; q += 64) {
-            const int j = q / w1, k = lo1 + (q - j * w1);
+            int j = (int)((float)q * inv_w1), kk1 = q - j * w1;  // q / w1, to within one
+            if (kk1 < 0) {
+              --j;
+              kk1 += w1;
+            } else if (kk1 >= w1) {
+              ++j;
+              kk1 -= w1;
+            }
+            const int k = lo1 + kk1;
             const int a0 = v.dp[j], a1 = v.dp[j + 1];
-            const int yk = k >= 1 ? y[k - 1] : -1;
+            const int yk = k >= 1 ? (yg ? yg[k - 1] : (int)s_y[wv][k - 1]) : -1;
             double r = 0.0;
-            if (a1 - a0 <= 8) {
-              // few arcs: all their loads in flight together
-              int sr[8], lb[8];
-              double pcv[8];
+            // four arcs at a time (a node has two or three), their loads in flight together
+            for (int a = a0; a < a1; a += 4) {
+              unsigned arc[4];
+              double pcv[4];
 #pragma unroll
-              for (int i = 0; i < 8; ++i) {
-                const bool in = a0 + i < a1;
-                sr[i] = in ? v.src[(a0 + i) * v.stride] : 0;
-                lb[i] = in ? v.lab[(a0 + i) * v.stride] : -2;
-                pcv[i] = in ? v.pc[a0 + i] : 0.0;
+              for (int i = 0; i < 4; ++i) {
+                const int ai = min(a + i, a1 - 1);
+                arc[i] = v.arc(ai);
+                pcv[i] = v.pc[ai];
               }
 #pragma unroll
-              for (int i = 0; i < 8; ++i) {
-                const int kk = lb[i] == 0 ? k : (lb[i] == yk ? k - 1 : -1);
-                if (kk >= lo && kk <= hi) r += cur[(size_t)sr[i] * W + (kk - lo)] * pcv[i];
-              }
-            } else {
-              for (int a = a0; a < a1; ++a) {
-                const int lab = v.lab[a * v.stride];
+              for (int i = 0; i < 4; ++i) {
+                const int lab = arc_label(arc[i]);
                 const int kk = lab == 0 ? k : (lab == yk ? k - 1 : -1);
-                if (kk < lo || kk > hi) continue;
-                r += cur[(size_t)v.src[a * v.stride] * W + (kk - lo)] * v.pc[a];
+                if (a + i < a1 && kk >= lo && kk <= hi)
+                  r += cur[(size_t)arc_src(arc[i]) * W + (kk - lo)] * pcv[i];
               }
             }
             nxt[(size_t)j * W + (k - lo1)] = r;
@@ -747,10 +756,8 @@ __global__ __launch_bounds__(kLT) void k_lat_seqscore(LatticeDev L, NBestDev N) 
             mx = wave_max_f64(mx);
             if (mx > 0.0) {
               const double inv = 1.0 / mx;
-              for (int q = lane; q < v.n1 * w1; q += 64) {
-                const int j = q / w1, k = lo1 + (q - j * w1);
-                nxt[(size_t)j * W + (k - lo1)] *= inv;
-              }
+              for (int j = 0; j < v.n1; ++j)
+                for (int k = lane; k < w1; k += 64) nxt[(size_t)j * W + k] *= inv;
               logscale += log(mx);
             }
           }
