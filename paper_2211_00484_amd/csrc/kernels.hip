@@ -630,7 +630,8 @@ __device__ __forceinline__ bool joiner_tile_of(int i, int n_ct, int& rt, int& ct
 template <bool BF16>
 __device__ __forceinline__ void stage_chunk(unsigned char* row, int cc, const uint4& v) {
   if (BF16) {
-    *reinterpret_cast<uint4*>(row + (size_t)cc * 16) = v;
+    // (by components: a whole-struct copy would keep the caller's array in scratch memory)
+    *reinterpret_cast<uint4*>(row + (size_t)cc * 16) = make_uint4(v.x, v.y, v.z, v.w);
   } else {
     unsigned char* p = row + (size_t)(cc >> 1) * 32 + (cc & 1) * 8;
     *reinterpret_cast<uint2*>(p) = make_uint2(v.x, v.y);
@@ -664,6 +665,23 @@ __device__ __forceinline__ void joiner_tile_small(const ModelDev& m, const JoinA
   const int col = n0 + 16 * wave + lr;
   const bool cvalid = col < V;
 
+  // The tile's h rows, for LDS: the first of a wave's loads, requested before anything is
+  // known of the rows (rows past the batch read its last; a row's products reach only its
+  // own results, which are dropped unless it is active).
+  constexpr int U = BF16 ? 4 : 8;                    // 16-byte chunks per thread and batch
+  const int ldk = Kpad + (BF16 ? 8 : 4);             // row stride in elements (16-byte pad)
+  const int cpr = Kpad * ESZ / 16;                   // 16-byte chunks per row
+  const int nchunk = BM * cpr;
+  const uint4* hsrc = reinterpret_cast<const uint4*>(a.h);
+  uint4 hv[U];
+  auto load_h = [&](int c0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int c = min(c0 + tid + u * 256, nchunk - 1), r = c / cpr;
+      hv[u] = hsrc[(size_t)min(r0 + r, a.R - 1) * cpr + (c - r * cpr)];
+    }
+  };
+  load_h(0);
   // W fragment of the first K chunk (registers) and the bias: issued before the
   // h staging so that all of the tile's loads are in flight together
   // (Kpad is a multiple of 512: one chunk of W per lane is 16 uint4 of bf16, or of high
@@ -698,28 +716,14 @@ __device__ __forceinline__ void joiner_tile_small(const ModelDev& m, const JoinA
   if (tid < BM) s_row[tid] = act ? r0 + tid : -1;
   if (!__syncthreads_or(act)) return;  // uniform: no row in this tile
 
-  // stage the tile's h rows in LDS (16-byte chunks, all loads in flight together)
-  const int ldk = Kpad + (BF16 ? 8 : 4);             // row stride in elements (16-byte pad)
-  const int cpr = Kpad * ESZ / 16;                   // 16-byte chunks per row
-  const int nchunk = BM * cpr;
-  const uint4* hsrc = reinterpret_cast<const uint4*>(a.h);
-  for (int base = tid; base < nchunk; base += 256 * 16) {
-    uint4 v[16];
+  for (int c0 = 0; c0 < nchunk; c0 += 256 * U) {
+    if (c0 > 0) load_h(c0);
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int c = base + u * 256;
-      v[u] = make_uint4(0, 0, 0, 0);
-      if (c < nchunk) {
-        const int r = c / cpr, row = s_row[r];
-        if (row >= 0) v[u] = hsrc[(size_t)row * cpr + (c - r * cpr)];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int c = base + u * 256;
+    for (int u = 0; u < U; ++u) {
+      const int c = c0 + tid + u * 256;
       if (c < nchunk) {
         const int r = c / cpr, cc = c - r * cpr;
-        stage_chunk<BF16>(smem + (size_t)r * ldk * ESZ, cc, v[u]);
+        stage_chunk<BF16>(smem + (size_t)r * ldk * ESZ, cc, hv[u]);
       }
     }
   }
@@ -2827,7 +2831,8 @@ __device__ __forceinline__ void stream_joiner(const ModelDev& m, const DecodeDev
   constexpr int ESZ = BF16 ? 2 : 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int V = m.V, Vpad = m.Vpad, nvt = d.nvt;
-  const int nch = m.Kpad / (KQ * CH);                  // chunks per column group
+  // chunks per column group (beyond C both operands are zeros: C = 32 takes one of 16)
+  const int nch = (m.C + KQ * CH - 1) / (KQ * CH);
   const int ncgw = (nvt - wave + 3) >> 2;              // column groups of this wave
   const int steps = ((ncgw + 1) >> 1) * nch;           // pairs of groups x chunks
   if (steps == 0) return;
