@@ -560,6 +560,12 @@ __device__ __forceinline__ bool joiner_row_active(const JoinArgs& a, int r) {
   return a.t < a.len[b] && j < a.nctx[b];
 }
 
+// Active rows of stream b (both loads at once: the count is read whether or not it is used)
+__device__ __forceinline__ int active_contexts(const JoinArgs& a, int b) {
+  const int len = a.len[b], n = a.nctx[b];
+  return a.t < len ? n : 0;
+}
+
 // The rows of a tile: entries [r0, r0 + BM) of the batch's active rows, in (stream,
 // context slot) order, into s_row (-1 past the last); false if there are none.  Rows are
 // b * Nc + j for the j < nctx[b] contexts of a stream within its length: packing them
@@ -576,7 +582,7 @@ __device__ __forceinline__ bool joiner_tile_rows(const JoinArgs& a, int r0, int*
   }
   const int per = (a.B + NT - 1) / NT, b0 = min(tid * per, a.B), b1 = min(b0 + per, a.B);
   int n = 0;
-  for (int b = b0; b < b1; ++b) n += a.t < a.len[b] ? a.nctx[b] : 0;
+  for (int b = b0; b < b1; ++b) n += active_contexts(a, b);
   for (int i = tid; i < BM; i += NT) s_row[i] = -1;
   const int incl = (int)wave_incl_scan_u32((unsigned)n);
   if (lane == 63) s_wsum[wave] = incl;
@@ -590,7 +596,7 @@ __device__ __forceinline__ bool joiner_tile_rows(const JoinArgs& a, int r0, int*
   }
   if (pos < r0 + BM && pos + n > r0)
     for (int b = b0; b < b1; ++b) {
-      const int nb = a.t < a.len[b] ? a.nctx[b] : 0;
+      const int nb = active_contexts(a, b);
       for (int j = max(0, r0 - pos); j < nb && pos + j < r0 + BM; ++j) s_row[pos + j - r0] = b * a.Nc + j;
       pos += nb;
     }
@@ -1215,7 +1221,7 @@ __global__ __launch_bounds__(kSweepThreads) void k_joiner_sweep(ModelDev m, Join
     b0 = min(tid * per, a.B);
     b1 = min(b0 + per, a.B);
     int n = 0;
-    for (int b = b0; b < b1; ++b) n += a.t < a.len[b] ? a.nctx[b] : 0;
+    for (int b = b0; b < b1; ++b) n += active_contexts(a, b);
     const int incl = (int)wave_incl_scan_u32((unsigned)n);
     if (lane == 63) s_wsum[wave] = incl;
     __syncthreads();
@@ -1234,7 +1240,7 @@ __global__ __launch_bounds__(kSweepThreads) void k_joiner_sweep(ModelDev m, Join
   const int nblk = (nrow + 15) / 16;
   if (!DENSE) {
     for (int b = b0; b < b1; ++b) {
-      const int nb = a.t < a.len[b] ? a.nctx[b] : 0;
+      const int nb = active_contexts(a, b);
       for (int j = max(0, r0 - pos); j < nb && pos + j < r0 + nrow; ++j) list[pos + j - r0] = b * a.Nc + j;
       pos += nb;
     }
