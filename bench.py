@@ -34,7 +34,10 @@ if ROOT not in sys.path:
 
 METRIC = "decoded frames/sec (B×T) at beam 4; joiner MFMA util %; prune HBM GB/s"
 # MI355X published peaks: fp32 matrix and fp32 vector are both 157.3 TFLOP/s
+# (the frame joiner's fp32 takes three products on the fp16 matrix units, which run at the
+# bf16 rate)
 PEAK = {"fp32_mfma_tflops": 157.3, "fp32_vector_tflops": 157.3, "bf16_mfma_tflops": 2500.0,
+        "fp32_pairs_tflops": 2500.0 / 3,
         "hbm_gbps": 8000.0}
 DEFAULT_STEPS = {"tiny": 50, "standard": 20, "graph": 20, "throughput": 10, "large": 10}
 KERNEL_SRC = os.path.join(ROOT, "paper_2211_00484_amd", "csrc", "kernels.hip")
@@ -210,7 +213,7 @@ def scaled_microbench(dtype: str, steps: int):
     j_us = 1e3 * (res[T2]["joiner"] - res[T1]["joiner"]) / nf
     s_bytes = work["search_bytes"] / nf
     j_flop = work["flop"] / nf
-    peak_j = PEAK["bf16_mfma_tflops"] if dtype == "bf16" else PEAK["fp32_mfma_tflops"]
+    peak_j = PEAK["bf16_mfma_tflops"] if dtype == "bf16" else PEAK["fp32_pairs_tflops"]
     line = {
         "microbenchmark": "scaled search + joiner, one frame at B = 8,192 (not a workload figure)",
         "config": {"model": "large (V=5,000, C=512)", "graph": "powerlaw1m", "B": B,
@@ -239,6 +242,8 @@ def decode_roofline(prof, K, work, dtype):
         kernels[name] = {"launches_per_step": n / K, "avg_us": 1e3 * ms / max(n, 1),
                          "ms_per_step": ms / K}
     sk = "stream_group" if "stream_group" in kernels else "stream"
+    if dtype != "bf16" and sk not in kernels:  # the frame joiner
+        peak_j = PEAK["fp32_pairs_tflops"]
     if sk in kernels:
         # one persistent kernel runs joiner and search for every frame: its joiner FLOP
         # and search bytes are both divided by the whole kernel's duration
@@ -532,7 +537,7 @@ def hyps_bench(args, w, inputs, model_np, model, graph, enc, dtype, K, W):
     model.set_profiling(False)
     kernels = {n: {"launches_per_step": c / K, "avg_us": 1e3 * ms / max(c, 1),
                    "ms_per_step": ms / K} for n, (c, ms) in prof.items() if c}
-    peak_j = PEAK["bf16_mfma_tflops"] if dtype == "bf16" else PEAK["fp32_mfma_tflops"]
+    peak_j = PEAK["bf16_mfma_tflops"] if dtype == "bf16" else PEAK["fp32_pairs_tflops"]
     j = kernels["joiner"]
     j_tflops = flop / j["launches_per_step"] / (j["avg_us"] * 1e-6) / 1e12
     # the step kernel reads each joiner row's logits and statistics once per selection
