@@ -545,7 +545,7 @@ struct JoinArgs {
   int* tk_c;
   float* z0;                // [R] (TOPK)
   int KT;
-  int R, n_rt, n_ct;        // rows; row and column tiles (128 x 128)
+  int R, n_rt, n_ct;        // rows; row tiles (sweep: row groups) and column tiles
   int nvt;                  // 64-column vocabulary tiles (stats and label lists)
   int rows_mode;            // 1: every row < R is active
   const int* len;
