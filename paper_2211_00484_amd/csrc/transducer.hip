@@ -9,8 +9,8 @@
 //  - k_transducer_ring, the usual one: the recursion in the linear domain (described
 //    with it);
 //  - k_transducer_logs, in the log domain: for grids whose ring does not fit the LDS, and
-//    (as a device function) for utterances with a log-probability that is not a finite
-//    number within [-300, 300].
+//    (as a device function) for utterances with an input that is not a number within
+//    [kRingMinLog, kRingMaxLog].
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -180,13 +180,16 @@ __global__ __launch_bounds__(kRingThreads) void k_transducer_logs(
 
 constexpr int kRingWorkers = kRingThreads - 64;
 constexpr int kRingLoads = 5;         // blank (and label) elements per worker and chunk
-// largest log-probability either way: a probability is then at least 2^-433, a term
-// 2^-434, and a term scaled down by kMaxShift still a normal number
-constexpr float kRingMaxLog = 300.f;
-constexpr int kMaxShift = 500;        // 2^-500 of a term is nothing beside one of 2^-434
+// Inputs the linear domain takes: e^x is then within [2^-433, 2^73] and a term (an input
+// times a mantissa) within [2^-434, 2^73].  A term may be scaled down by up to kMaxShift: it
+// stays a normal number (2^-1004), and whatever is scaled down that far (an unreachable
+// cell, a term that many powers of two below) is at most 2^-497, nothing beside a live term.
+// (Log-probabilities are at most 0; the room above it is for unnormalised scores.)
+constexpr float kRingMinLog = -300.f, kRingMaxLog = 50.f;
+constexpr int kMaxShift = 570;
 constexpr int kZeroExp = -(1 << 29);  // exponent of an unreachable cell; any below half of
                                       // it counts as one
-constexpr int kRingMaxSteps = 200000; // (steps * 300 / ln 2 stays above kZeroExp)
+constexpr int kRingMaxSteps = 200000; // (steps * 2 * 300 / ln 2 stays above kZeroExp / 2)
 constexpr size_t kRingLds = kMaxLds - 1024;
 
 // A double's exponent field, as its high word's integer units.
@@ -350,17 +353,24 @@ __global__ __launch_bounds__(kRingThreads, K <= 4 ? 4 : 2) void k_transducer_rin
       }
     };
     const ExpLogProb exp_log_prob;
-    unsigned worst = 0;  // largest |x| seen, as bits (a NaN's are above any number's)
+    // the largest and the most negative input seen, as bits (as integers of either kind a
+    // NaN's are beyond any number's of its sign)
+    int highest = 0;
+    unsigned lowest = 0;
+    auto note = [&](float x) {
+      highest = max(highest, __float_as_int(x));
+      lowest = max(lowest, __float_as_uint(x));
+    };
     int c0 = 0;          // ring cell of the next chunk's first row
     auto produce = [&]() {
 #pragma unroll
       for (int q = 0; q < kRingLoads; ++q) {
         if (bcell[q] >= 0) {
-          worst = max(worst, __float_as_uint(xb[q]) & 0x7fffffffu);
+          note(xb[q]);
           reinterpret_cast<double*>(cells + c0 + bcell[q])[0] = exp_log_prob(xb[q]);
         }
         if (lcell[q] >= 0) {
-          worst = max(worst, __float_as_uint(xl[q]) & 0x7fffffffu);
+          note(xl[q]);
           reinterpret_cast<double*>(cells + c0 + lcell[q])[1] = exp_log_prob(xl[q]);
         }
       }
@@ -379,7 +389,7 @@ __global__ __launch_bounds__(kRingThreads, K <= 4 ? 4 : 2) void k_transducer_rin
       if (c + 1 < nchunks) produce();
       if (c + 2 < nchunks) request((c + 2) * R);
       if (ALPHA) store_rows((c - 1) * R - lag, c * R - lag, w, kRingWorkers);
-      if (worst > __float_as_uint(kRingMaxLog)) s_bad = 1;
+      if (highest > __float_as_int(kRingMaxLog) || lowest > __float_as_uint(kRingMinLog)) s_bad = 1;
       lds_barrier();
     }
   } else {

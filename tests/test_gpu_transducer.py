@@ -113,6 +113,30 @@ def test_ring_shapes(kind, B, T, U):
 
 
 @pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("hi,lo", [(200.0, -200.0), (170.0, -170.0), (290.0, -290.0), (49.0, -299.0),
+                                   (51.0, -299.0), (0.0, -299.0), (20.0, -299.0)])
+def test_large_scores_of_both_signs(kind, hi, lo):
+    """Unnormalised scores far above 0 beside ones far below it, on both sides of the linear
+    domain's limits: a negligible term scaled up must not pass a live one."""
+    blank = np.full((6, 1, 2), hi, np.float32)
+    label = np.full((6, 1, 1), lo, np.float32)
+    blank[1], label[1] = lo, hi
+    blank[2, :, 1] = lo
+    blank[3, :, 0] = lo
+    blank[4], label[4] = lo, lo
+    blank[5], label[5] = hi, hi
+    ones = np.ones(6, np.int32)
+    _check(kind, blank, label, ones, ones)
+    rng = np.random.default_rng(int(hi - lo))
+    blank = rng.uniform(lo, hi, size=(5, 30, 11)).astype(np.float32)
+    label = rng.uniform(lo, hi, size=(5, 30, 10)).astype(np.float32)
+    # cells reached only through the lowest values, next to unreachable ones
+    blank[3, :, :], label[3, :, :] = lo, hi
+    blank[4, :, :], label[4, :, :] = hi, lo
+    _check(kind, blank, label, np.full(5, 30, np.int32), np.full(5, 10, np.int32))
+
+
+@pytest.mark.parametrize("kind", KINDS)
 def test_extreme_log_probabilities(kind):
     """Values on both sides of what the linear domain takes: steep ones of -299, and
     utterances with -inf, -1e30 or 1e3 among ordinary ones.  A NaN in a cell that is not
