@@ -26,8 +26,9 @@ __device__ __forceinline__ double ninf() { return -__builtin_inf(); }
 
 // (a call: inlined, the two transcendental functions would set the kernels' register count)
 __device__ __attribute__((noinline)) double log_add2(double a, double b) {
-  const double hi = fmax(a, b), lo = fmin(a, b);
-  return hi == ninf() ? hi : hi + log1p(exp(lo - hi));
+  const bool ge = a >= b;  // (fmax and fmin would drop a NaN)
+  const double hi = ge ? a : b, lo = ge ? b : a;
+  return lo == ninf() ? hi : hi + log1p(exp(lo - hi));
 }
 
 // Workgroup barrier that orders LDS accesses only: global loads requested ahead of it stay

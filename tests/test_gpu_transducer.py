@@ -160,6 +160,7 @@ def test_extreme_log_probabilities(kind):
     want, _ = oracle.transducer_forward(kind, blank[:7], label[:7], frames[:7], labels[:7])
     total = total.cpu().numpy()
     assert (status.cpu().numpy() == 0).all()
+    assert np.isnan(total[7])
     fin = np.isfinite(want)
     assert np.array_equal(total[:7][~fin], want[~fin])
     assert np.allclose(total[:7][fin], want[fin], rtol=1e-9, atol=1e-9)
