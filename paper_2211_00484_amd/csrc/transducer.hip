@@ -479,6 +479,7 @@ __global__ __launch_bounds__(kRingThreads, K <= 4 ? 4 : 2) void k_transducer_rin
     }
   }
   if (s_bad) {  // uniform: an input the linear domain does not take
+    __syncthreads();  // the alpha rows stored so far are complete before others store theirs
     log_recursion<KIND>(blank, label, Tb, Ub, b, T, U, total, alpha, status,
                         reinterpret_cast<double*>(cells));
     return;
