@@ -24,12 +24,75 @@ constexpr int kRingThreads = 512;  // both kernels
 
 __device__ __forceinline__ double ninf() { return -__builtin_inf(); }
 
-// (a call: inlined, the two transcendental functions would set the kernels' register count)
-__device__ __attribute__((noinline)) double log_add2(double a, double b) {
-  const bool ge = a >= b;  // (fmax and fmin would drop a NaN)
-  const double hi = ge ? a : b, lo = ge ? b : a;
-  return lo == ninf() ? hi : hi + log1p(exp(lo - hi));
+// A double's exponent field, as its high word's integer units.
+__device__ __forceinline__ unsigned hi_word(double x) {
+  return (unsigned)((unsigned long long)__double_as_longlong(x) >> 32);
 }
+__device__ __forceinline__ double with_hi(double x, unsigned hi) {
+  const unsigned lo = (unsigned)(unsigned long long)__double_as_longlong(x);
+  return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
+}
+// x 2^n, for results that are normal numbers
+__device__ __forceinline__ double scaled(double x, int n) {
+  return with_hi(x, hi_word(x) + ((unsigned)n << 20));
+}
+
+// log(e^a + e^b); a term below e^-300 of the other adds nothing.  The series: e^f = 1 + f +
+// ... + f^12 / 12! with |f| <= ln 2 / 2, and log z = 2 (s + s^3 / 3 + ... + s^21 / 21) with
+// s = (z - 1) / (z + 1), z = 1 + e^(lo - hi) or half of it above sqrt 2 (|s| < 0.172).  The
+// steps of the log-domain recursion are a chain of these: no branches, the constants in scalar
+// registers.
+struct LogAdd {
+  double e[11], l[10];
+  double log2e = 1.4426950408889634, shift = 6755399441055744.0;
+  double ln2 = 0.69314718055994529, ln2_lo = 2.3190468138462996e-17;  // ln 2 and its rounding
+  __device__ __forceinline__ LogAdd() {
+    double f = 2.0;
+#pragma unroll
+    for (int n = 0; n < 11; ++n) {
+      e[n] = 1.0 / f;  // 1 / (n + 2)!
+      f *= n + 3;
+      asm("" : "+s"(e[n]));
+    }
+#pragma unroll
+    for (int n = 0; n < 10; ++n) {
+      l[n] = 1.0 / (2 * n + 3);
+      asm("" : "+s"(l[n]));
+    }
+    asm("" : "+s"(log2e), "+s"(shift), "+s"(ln2), "+s"(ln2_lo));
+  }
+  __device__ __forceinline__ double operator()(double a, double b) const {
+    const bool ge = a >= b;  // (fmax and fmin would drop a NaN)
+    const double hi = ge ? a : b, lo = ge ? b : a, d = lo - hi;
+    const bool near = d >= -300.0;
+    const double x = near ? d : -300.0;
+    const double t = __builtin_fma(x, log2e, shift), k = t - shift;
+    const double f = __builtin_fma(-k, ln2_lo, __builtin_fma(-k, ln2, x));
+    double p = e[10];
+#pragma unroll
+    for (int n = 9; n >= 0; --n) p = __builtin_fma(p, f, e[n]);
+    p = __builtin_fma(p, f, 1.0);
+    p = __builtin_fma(p, f, 1.0);
+    const double y = scaled(p, (int)(unsigned)(unsigned long long)__double_as_longlong(t));
+    const bool half = y > 0.41421356237309503;
+    const double den = y + (half ? 3.0 : 2.0), num = half ? y - 1.0 : y;
+    double r = __builtin_amdgcn_rcp(den);
+    r = r * __builtin_fma(-den, r, 2.0);  // two Newton steps
+    r = r * __builtin_fma(-den, r, 2.0);
+    const double s = num * r, s2 = s * s;
+    double q = l[9];
+#pragma unroll
+    for (int n = 8; n >= 0; --n) q = __builtin_fma(q, s2, l[n]);
+    q = __builtin_fma(q, s2, 1.0);
+    const double sum = hi + __builtin_fma(2.0 * s, q, half ? ln2 : 0.0);
+    return near ? sum : lo == ninf() || d == d ? hi : d;
+  }
+};
+
+// Pointers of the log-domain recursion, a called function: accesses by generic ones would
+// count as both kinds, and each wait for LDS data would be one for the loads in flight.
+typedef __attribute__((address_space(3))) double lds_double;
+typedef __attribute__((address_space(1))) float global_float;
 
 // Workgroup barrier that orders LDS accesses only: global loads requested ahead of it stay
 // in flight across it (a full barrier waits for them, a memory round trip per chunk).
@@ -44,18 +107,25 @@ __device__ __forceinline__ void lds_barrier() {
 // eq. (1) also depends on its own left neighbour, the cells with t + u = s (eq. 1), from
 // the state after step s - 1.  buf: [2][U + 1] doubles of LDS.  One log-add and one
 // barrier per step, the next step's inputs in flight meanwhile.
+// Bound: the log-add's instructions.  MI355X, with the ring's pass before it: modified,
+// T = 250, U = 80, an infinity in every utterance: B = 32 127 us, B = 1,024 302 us (the
+// library's exp and log1p and waits for every load: 225 and 560; one wave per utterance and
+// no ring: 247 and 297).  By itself: standard, T = 500, U = 400, B = 4 680 us (1,070; 4,610).
 template <int KIND>
 __device__ __attribute__((noinline)) void log_recursion(const float* __restrict__ blank,
                                                         const float* __restrict__ label, int Tb,
                                                         int Ub, int b, int T, int U,
                                                         double* __restrict__ total,
                                                         float* __restrict__ alpha,
-                                                        int* __restrict__ status, double* buf) {
+                                                        int* __restrict__ status, lds_double* buf) {
   constexpr int Q = 64 * kTransducerMaxK / kRingThreads;  // cells per thread
-  const int tid = threadIdx.x, U1 = U + 1;
-  const float* bl = blank + (size_t)b * T * U1;
-  const float* lb = label + (size_t)b * T * U;
-  float* al = alpha ? alpha + (size_t)b * (T + 1) * U1 : nullptr;
+  const LogAdd log_add;
+  // Short rows leave most waves idle; which ones work turns with the utterance, so that the
+  // workgroups of a compute unit (every 256th, as they are handed out) load all its SIMDs.
+  const int tid = (threadIdx.x + 128 * ((b + (b >> 8)) & 3)) % kRingThreads, U1 = U + 1;
+  const global_float* bl = (const global_float*)blank + (size_t)b * T * U1;
+  const global_float* lb = U > 0 ? (const global_float*)label + (size_t)b * T * U : bl;
+  global_float* al = alpha ? (global_float*)alpha + (size_t)b * (T + 1) * U1 : nullptr;
   constexpr int kOut = KIND == 0 ? 0 : 1;  // alpha row of row i: i + kOut
   for (int u = tid; u < U1; u += kRingThreads) {
     const double v = u == 0 ? 0.0 : ninf();
@@ -70,22 +140,23 @@ __device__ __attribute__((noinline)) void log_recursion(const float* __restrict_
     i = KIND == 0 ? s - u : s;
     return i >= 0 && i < Tb && u <= Ub;
   };
+  // inputs of the next step (of a cell that is inactive, another's: no branches around the
+  // loads, which would make the step wait for all of them)
   float xb[Q], xl[Q];
   auto request = [&](int s) {
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      const int u = tid + q * kRingThreads;
-      int i;
-      const bool act = active(s, u, i);
-      xb[q] = act && (KIND != 0 || i > 0) ? bl[(size_t)(i - 1 + kOut) * U1 + u] : 0.f;
-      xl[q] = act && u > 0 ? lb[(size_t)i * U + u - 1] : 0.f;
+      const int u = min(tid + q * kRingThreads, Ub);
+      const int i = min(max(KIND == 0 ? s - u : s, 0), Tb - 1);
+      xb[q] = bl[(size_t)max(i - 1 + kOut, 0) * U1 + u];
+      xl[q] = lb[(size_t)i * U + max(u - 1, 0)];
     }
   };
   request(0);
   lds_barrier();
   for (int s = 0; s < steps; ++s) {
-    const double* prev = buf + (s & 1) * U1;
-    double* next = buf + (~s & 1) * U1;
+    const lds_double* prev = buf + (s & 1) * U1;
+    lds_double* next = buf + (~s & 1) * U1;
     float cb[Q], cl[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
@@ -98,20 +169,15 @@ __device__ __attribute__((noinline)) void log_recursion(const float* __restrict_
       const int u = tid + q * kRingThreads;
       if (u >= U1) continue;
       int i;
-      double v = prev[u];
-      if (active(s, u, i)) {
-        if (KIND == 0 && i == 0)
-          v = u == 0 ? 0.0 : ninf();
-        else
-          v += (double)cb[q];
-        if (u > 0) {
-          double w = prev[u - 1] + (double)cl[q];
-          if (KIND == 2) w += (double)cb[q];
-          v = log_add2(v, w);
-        }
-        if (al) al[(size_t)(i + kOut) * U1 + u] = (float)v;
-      }
-      next[u] = v;
+      const bool act = active(s, u, i);
+      const double old = prev[u];
+      double v = old + (double)cb[q];
+      if (KIND == 0 && i == 0) v = u == 0 ? 0.0 : ninf();
+      double w = prev[max(u - 1, 0)] + (double)cl[q];
+      if (KIND == 2) w += (double)cb[q];
+      v = log_add(v, u > 0 ? w : ninf());
+      if (al && act) al[(size_t)(i + kOut) * U1 + u] = (float)v;
+      next[u] = act ? v : old;
     }
     lds_barrier();
   }
@@ -145,7 +211,7 @@ __global__ __launch_bounds__(kRingThreads) void k_transducer_logs(
   const int b = blockIdx.x;
   int Tb, Ub;
   if (!utterance(lengths, b, T, U, total, status, threadIdx.x == 0, Tb, Ub)) return;
-  log_recursion<KIND>(blank, label, Tb, Ub, b, T, U, total, alpha, status, buf);
+  log_recursion<KIND>(blank, label, Tb, Ub, b, T, U, total, alpha, status, (lds_double*)buf);
 }
 
 // ---------------------------------------------------------------------------
@@ -192,19 +258,6 @@ constexpr int kZeroExp = -(1 << 29);  // exponent of an unreachable cell; any be
                                       // it counts as one
 constexpr int kRingMaxSteps = 200000; // (steps * 2 * 300 / ln 2 stays above kZeroExp / 2)
 constexpr size_t kRingLds = kMaxLds - 1024;
-
-// A double's exponent field, as its high word's integer units.
-__device__ __forceinline__ unsigned hi_word(double x) {
-  return (unsigned)((unsigned long long)__double_as_longlong(x) >> 32);
-}
-__device__ __forceinline__ double with_hi(double x, unsigned hi) {
-  const unsigned lo = (unsigned)(unsigned long long)__double_as_longlong(x);
-  return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
-}
-// x 2^n, for results that are normal numbers
-__device__ __forceinline__ double scaled(double x, int n) {
-  return with_hi(x, hi_word(x) + ((unsigned)n << 20));
-}
 
 // e^x for |x| <= 300, to about 2e-16: x = k ln 2 + f, Taylor series in f up to f^12 / 12!
 // (|f| <= ln 2 / 2, so the rest is below 2e-16).  k comes out of the low bits of
@@ -281,13 +334,13 @@ constexpr int kRingGroup = K <= 2 ? 4 : K == 4 ? 2 : 1;
 // U / K;
 // rs: cells per ring row, at least U + 1 rounded up to K.
 template <int K, int KIND, bool ALPHA>
-__global__ __launch_bounds__(kRingThreads, K <= 4 ? 4 : 2) void k_transducer_ring(
+__global__ __launch_bounds__(kRingThreads, K <= 4 || (K == 8 && KIND != 0) ? 4 : 2) void k_transducer_ring(
     const float* __restrict__ blank, const float* __restrict__ label,
     const int* __restrict__ lengths, int T, int U, double* __restrict__ total,
     float* __restrict__ alpha, int* __restrict__ status, int R, int ring, int rs) {
   constexpr int G = kRingGroup<K>;
   extern __shared__ __align__(16) double2 cells[];  // [ring][rs]
-  __shared__ int s_bad;
+  __shared__ int s_bad[2];  // set in even and in odd groups of four chunks
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   int Tb, Ub;
   if (!utterance(lengths, b, T, U, total, status, tid == 0, Tb, Ub)) return;  // uniform
@@ -315,7 +368,15 @@ __global__ __launch_bounds__(kRingThreads, K <= 4 ? 4 : 2) void k_transducer_rin
     }
   };
 
-  if (tid == 0) s_bad = 0;
+  if (tid < 2) s_bad[tid] = 0;
+  // An input the linear domain does not take ends both loops within the next group of chunks:
+  // while a group reads the flag of the one before, only its own can be set, so all waves
+  // see the same.  (Not for eq. (1): the check alone costs its loop 3%, and its fallback is
+  // shorter than what it replaces by more than the ring's pass.)
+  int end_chunk = nchunks;
+  auto seen = [&](int c) {
+    return KIND != 0 && c > 0 && c % 4 == 0 && __builtin_amdgcn_readfirstlane(s_bad[~(c / 4) & 1]) != 0;
+  };
   if (tid >= 64) {
     // Worker w handles elements j = w, w + kRingWorkers, ... of a chunk's R x U1 blank and
     // R x U label values.  A chunk's rows are consecutive in memory and (ring being a
@@ -386,11 +447,12 @@ __global__ __launch_bounds__(kRingThreads, K <= 4 ? 4 : 2) void k_transducer_rin
     produce();
     request(R);
     lds_barrier();
-    for (int c = 0; c < nchunks; ++c) {
+    for (int c = 0; c < end_chunk; ++c) {
+      if (seen(c)) end_chunk = c;  // (this chunk's work is harmless)
       if (c + 1 < nchunks) produce();
       if (c + 2 < nchunks) request((c + 2) * R);
       if (ALPHA) store_rows((c - 1) * R - lag, c * R - lag, w, kRingWorkers);
-      if (highest > __float_as_int(kRingMaxLog) || lowest > __float_as_uint(kRingMinLog)) s_bad = 1;
+      if (highest > __float_as_int(kRingMaxLog) || lowest > __float_as_uint(kRingMinLog)) s_bad[c / 4 & 1] = 1;
       lds_barrier();
     }
   } else {
@@ -453,7 +515,8 @@ __global__ __launch_bounds__(kRingThreads, K <= 4 ? 4 : 2) void k_transducer_rin
       }
     };
     lds_barrier();
-    for (int c = 0; c < nchunks; ++c) {
+    for (int c = 0; c < end_chunk; ++c) {
+      if (seen(c)) end_chunk = c;  // (this chunk's work is harmless)
       fetch(pa, sa);
       for (int g0 = 0; g0 < R; g0 += 2 * G) {
         fetch(pb, sb);
@@ -463,7 +526,7 @@ __global__ __launch_bounds__(kRingThreads, K <= 4 ? 4 : 2) void k_transducer_rin
       }
       lds_barrier();
     }
-    if (lane == Ub / K && !s_bad) {
+    if (lane == Ub / K && !(s_bad[0] | s_bad[1])) {
       double mine = 0.5;
       int exp2 = kZeroExp;
 #pragma unroll
@@ -478,10 +541,10 @@ __global__ __launch_bounds__(kRingThreads, K <= 4 ? 4 : 2) void k_transducer_rin
       if (status) status[b] = 0;
     }
   }
-  if (s_bad) {  // uniform: an input the linear domain does not take
+  if (s_bad[0] | s_bad[1]) {  // uniform
     __syncthreads();  // the alpha rows stored so far are complete before others store theirs
     log_recursion<KIND>(blank, label, Tb, Ub, b, T, U, total, alpha, status,
-                        reinterpret_cast<double*>(cells));
+                        (lds_double*)cells);
     return;
   }
   if (ALPHA) store_rows((nchunks - 1) * R - lag, Tb, tid, kRingThreads);

@@ -137,6 +137,20 @@ def test_large_scores_of_both_signs(kind, hi, lo):
 
 
 @pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("B,T,U", [(24, 150, 80), (6, 70, 300), (520, 40, 20)])
+def test_impossible_cells(kind, B, T, U):
+    """An infinity in one cell of every second utterance, in any row from the first to the
+    last: noticed in any chunk, also when the linear domain has begun to store alpha."""
+    blank, label, _, _ = _inputs(B + U, B, T, U)
+    for b in range(0, B, 2):
+        row = (b // 2) * (T - 1) // max(1, (B - 1) // 2)
+        x = blank if b % 4 == 0 else label
+        x[b, min(row, T - 1), (5 * b) % U] = -np.inf
+    frames, labels = np.full(B, T, np.int32), np.full(B, min(U, T), np.int32)
+    _check(kind, blank, label, frames, labels)
+
+
+@pytest.mark.parametrize("kind", KINDS)
 def test_extreme_log_probabilities(kind):
     """Values on both sides of what the linear domain takes: steep ones of -299, and
     utterances with -inf, -1e30 or 1e3 among ordinary ones.  A NaN in a cell that is not
