@@ -810,7 +810,7 @@ tbs_status tbs_model_create(int32_t vocab_size, int32_t dim, int32_t context_siz
   {
     const size_t wb = m->bf16 ? 2 : 4;  // bytes per packed weight (an fp16 pair: 4)
     const size_t sizes[7] = {VK * 4, VK * 4, VpK * wb, m->bf16 ? 0 : VpK * wb, VpK * wb,
-                             (size_t)m->V * 4, 8};
+                             (size_t)m->V * 4, m->bf16 ? 0 : (size_t)m->Vpad * 4};
     char* at[7] = {};
     size_t total = 0, largest = 0;
     for (size_t n : sizes) {

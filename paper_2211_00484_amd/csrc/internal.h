@@ -37,21 +37,23 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
   return (uint16_t)(u >> 16);
 }
 
-// The frame joiner's fp32 operands travel as pairs of fp16, x = high + low to about 2^-23
-// of x: h scaled by 2^14, W by a power of two per model that takes its largest magnitude
-// to [2^13, 2^14), so that high parts stay clear of fp16's limits and low parts (down to
-// 2^-24) resolve 2^-39 of the largest magnitude.  A product is then three on the fp16
-// matrix units (high x high, high x low, low x high; low x low is below 2^-22 of it).
+// The frame joiner's fp32 operands travel as pairs of fp16, x = high + 2^-12 low to 2^-23
+// of x: h scaled by 2^14, a row of W (one label's weights) by the power of two that takes
+// its largest magnitude to [2^13, 2^14), so that high parts stay clear of fp16's limits.
+// The low part, scaled too, keeps its 11 bits while the high part is a normal number: down
+// to 2^-28 of the row's largest magnitude (of 1 for h); below that the pair is still within
+// 2^-51 of it.  A product is three on the fp16 matrix units (high x high; high x low and
+// low x high, summed apart and scaled by 2^-12; low x low is below 2^-22 of it).
 // Rows of h hold four values in 16 bytes (their high parts, then their low parts), W eight
 // in 32.
-constexpr float kHScale = 16384.f;
+constexpr float kHScale = 16384.f, kLowScale = 4096.f;
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint16_t f16_bits(_Float16 x) { return __builtin_bit_cast(uint16_t, x); }
 // (an infinite or NaN x keeps it in the high part)
 __device__ __forceinline__ void f32_split(float x, uint16_t& hi, uint16_t& lo) {
   const _Float16 a = (_Float16)x;
-  const float r = x - (float)a;
+  const float r = (x - (float)a) * kLowScale;
   hi = f16_bits(a);
   lo = f16_bits((_Float16)(fabsf(r) < INFINITY ? r : 0.f));
 }
@@ -61,14 +63,18 @@ __device__ __forceinline__ void store_split(void* base, size_t row0, int k, floa
   const float x = h * kHScale;
   const _Float16 a = (_Float16)x;
   p[0] = f16_bits(a);
-  p[4] = f16_bits((_Float16)(x - (float)a));
+  p[4] = f16_bits((_Float16)((x - (float)a) * kLowScale));
 }
 __device__ __forceinline__ void split_pair(float h0, float h1, unsigned& hi, unsigned& lo) {
   const f32x2 x = {h0 * kHScale, h1 * kHScale};
   const f16x2 a = __builtin_convertvector(x, f16x2);
-  const f32x2 r = {x[0] - (float)a[0], x[1] - (float)a[1]};
+  const f32x2 r = {(x[0] - (float)a[0]) * kLowScale, (x[1] - (float)a[1]) * kLowScale};
   hi = __builtin_bit_cast(unsigned, a);
   lo = __builtin_bit_cast(unsigned, __builtin_convertvector(r, f16x2));
+}
+// The logit's products from their two sums, zscale the row's inverse scale.
+__device__ __forceinline__ float unsplit(float high, float cross, float zscale) {
+  return __builtin_fmaf(cross, 1.f / kLowScale, high) * zscale;
 }
 
 // tanh for the joiner input: (e - 1) / (e + 1), e = exp(2x), with x clamped to [-9, 9]
@@ -88,7 +94,7 @@ struct ModelDev {
   const uint16_t* Ws;       // [Vpad][Kpad] joiner weight as fp16 pairs (fp32 mode)
   const uint16_t* Wsi;      // [Kpad/8][2][Vpad][8] the same, high and low parts interleaved
                             // by 16-byte k slices (small frame-joiner tiles)
-  const float* zscale;      // [0]: logit = zscale * (sum of products of scaled pairs)
+  const float* zscale;      // [Vpad]: logit = zscale * (sum of products of scaled pairs)
   const uint16_t* Wb;       // [Vpad][Kpad] bf16 joiner weight (bf16 mode)
   const void* Wi;           // [Kpad/KQ][Vpad][KQ] W interleaved by 16-byte k slices (KQ = 4 fp32
                             // or 8 bf16), read by the per-stream kernel

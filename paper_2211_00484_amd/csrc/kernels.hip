@@ -212,63 +212,99 @@ __device__ __forceinline__ float logp_of(float z, double lse) { return (float)((
 // consecutive vocabulary columns read one contiguous kilobyte (per-stream kernels, bf16
 // small tiles); Wsi is the split W the same way, [Kpad / 8][high, low][Vpad][8].
 
-// Largest finite |W| (as bits) into wmax, which starts at 0.
-__global__ __launch_bounds__(256) void k_weight_max(const float* __restrict__ W, long long n,
-                                                    unsigned* __restrict__ wmax) {
-  unsigned v = 0;
-  for (long long i = blockIdx.x * 256ll + threadIdx.x; i < n; i += gridDim.x * 256ll) {
-    const unsigned u = __float_as_uint(W[i]) & 0x7fffffffu;
-    if (u < 0x7f800000u) v = max(v, u);
-  }
-  v = wave_max_u32(v);
-  if ((threadIdx.x & 63) == 0) atomicMax(wmax, v);
-}
 
-// Exponent s of the power of two that takes a joiner weight's largest magnitude to
+// Exponent s of the power of two that takes a row's largest magnitude (as bits) to
 // [2^13, 2^14), within the range whose inverse (and that of h) fp32 can hold.
 __device__ __forceinline__ int split_exponent(unsigned wmax) {
   const int e = (int)(wmax >> 23) - 127;  // wmax in [2^e, 2^(e+1)), or 0
   return wmax == 0 ? 0 : min(13 - e, 112);
 }
 
-__global__ void k_model_setup(const float* __restrict__ E, const float* __restrict__ conv,
-                              const float* __restrict__ W, const float* __restrict__ b_out, int V,
-                              int C, int Kpad, int Vpad, int bf16, float* __restrict__ P0,
-                              float* __restrict__ P1, uint16_t* __restrict__ Ws,
-                              uint16_t* __restrict__ Wsi, float* __restrict__ zscale,
-                              uint16_t* __restrict__ Wb, void* __restrict__ Wi,
-                              float* __restrict__ bias) {
-  const long long n = (long long)Vpad * Kpad;
-  // zscale: the largest |W| on entry (bits, second word); z = zscale[0] * (scaled sum)
-  const int sexp = bf16 ? 0 : split_exponent(reinterpret_cast<const unsigned*>(zscale)[1]);
-  if (!bf16 && blockIdx.x == 0 && threadIdx.x == 0) zscale[0] = ldexpf(1.f / kHScale, -sexp);
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
-    const int v = (int)(i / Kpad), k = (int)(i - (long long)v * Kpad);
-    const bool in = v < V && k < C;
-    const float e = in ? E[(size_t)v * C + k] : 0.f;
-    const float w = in ? W[(size_t)v * C + k] : 0.f;
-    if (v < V) {
-      P0[i] = in ? conv[2 * k + 0] * e : 0.f;
-      P1[i] = in ? conv[2 * k + 1] * e : 0.f;
-    }
-    if (bf16) {
-      const uint16_t wb = f32_to_bf16_rne(w);
-      Wb[i] = wb;
-      reinterpret_cast<uint16_t*>(Wi)[((size_t)(k >> 3) * Vpad + v) * 8 + (k & 7)] = wb;
+// Columns [k, k + 8) of a row of C, zeros beyond; vec: 16-byte loads (C a multiple of 4).
+__device__ __forceinline__ void load8(const float* __restrict__ row, int k, int C, bool vec, float (&x)[8]) {
+#pragma unroll
+  for (int j = 0; j < 8; j += 4)
+    if (vec) {
+      const float4 v = k + j < C ? *reinterpret_cast<const float4*>(row + k + j) : make_float4(0, 0, 0, 0);
+      x[j] = v.x, x[j + 1] = v.y, x[j + 2] = v.z, x[j + 3] = v.w;
     } else {
-      uint16_t hi, lo;
-      f32_split(ldexpf(w, sexp), hi, lo);
-      uint16_t* row = Ws + (size_t)v * Kpad * 2 + (k >> 3) * 16 + (k & 7);
-      row[0] = hi;
-      row[8] = lo;
-      uint16_t* col = Wsi + ((size_t)(k >> 3) * 2 * Vpad + v) * 8 + (k & 7);
-      col[0] = hi;
-      col[(size_t)Vpad * 8] = lo;
-      reinterpret_cast<float*>(Wi)[((size_t)(k >> 2) * Vpad + v) * 4 + (k & 3)] = w;
+      for (int i = 0; i < 4; ++i) x[j + i] = k + j + i < C ? row[k + j + i] : 0.f;
     }
-    if (k == 0 && v < V) bias[v] = b_out ? b_out[v] : 0.f;
+}
+
+// One wave per vocabulary row, eight columns per lane and step.
+__global__ __launch_bounds__(256) void k_model_setup(
+    const float* __restrict__ E, const float* __restrict__ conv, const float* __restrict__ W,
+    const float* __restrict__ b_out, int V, int C, int Kpad, int Vpad, int bf16,
+    float* __restrict__ P0, float* __restrict__ P1, uint16_t* __restrict__ Ws,
+    uint16_t* __restrict__ Wsi, float* __restrict__ zscale, uint16_t* __restrict__ Wb,
+    void* __restrict__ Wi, float* __restrict__ bias) {
+  const int lane = threadIdx.x & 63, v = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (v >= Vpad) return;  // whole wave
+  const bool in = v < V;
+  const int Cv = in ? C : 0;  // rows past the vocabulary are zeros
+  const float* w_row = W + (size_t)(in ? v : 0) * C;
+  const float* e_row = E + (size_t)(in ? v : 0) * C;
+  const bool vec = C % 4 == 0 &&
+                   ((reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(E) |
+                     reinterpret_cast<uintptr_t>(conv)) & 15) == 0;
+  int sexp = 0;
+  if (!bf16) {
+    unsigned wmax = 0;  // largest finite magnitude
+    for (int k = 8 * lane; k < Cv; k += 512) {
+      float w[8];
+      load8(w_row, k, Cv, vec, w);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const unsigned u = __float_as_uint(w[j]) & 0x7fffffffu;
+        if (u < 0x7f800000u) wmax = max(wmax, u);
+      }
+    }
+    sexp = split_exponent(wave_max_u32(wmax));
+    if (lane == 0) zscale[v] = ldexpf(1.f / kHScale, -sexp);
   }
+  for (int k = 8 * lane; k < Kpad; k += 512) {
+    float w[8], e[8];
+    load8(w_row, k, Cv, vec, w);
+    load8(e_row, k, Cv, vec, e);
+    if (in) {
+      const size_t o = (size_t)v * Kpad + k;
+      float t[2][8];  // the taps of columns k .. k + 7, in pairs
+      load8(conv, 2 * k, 2 * C, vec, t[0]);
+      load8(conv, 2 * k + 8, 2 * C, vec, t[1]);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const float* x = e + 4 * j;
+        *reinterpret_cast<float4*>(P0 + o + 4 * j) =
+            make_float4(t[j][0] * x[0], t[j][2] * x[1], t[j][4] * x[2], t[j][6] * x[3]);
+        *reinterpret_cast<float4*>(P1 + o + 4 * j) =
+            make_float4(t[j][1] * x[0], t[j][3] * x[1], t[j][5] * x[2], t[j][7] * x[3]);
+      }
+    }
+    const size_t row8 = ((size_t)v * Kpad + k) / 8, col8 = (size_t)(k >> 3) * Vpad + v;
+    union {
+      uint16_t h[8];
+      uint4 q;
+    } hi, lo;
+    if (bf16) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) hi.h[j] = f32_to_bf16_rne(w[j]);
+      reinterpret_cast<uint4*>(Wb)[row8] = hi.q;
+      reinterpret_cast<uint4*>(Wi)[col8] = hi.q;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) f32_split(ldexpf(w[j], sexp), hi.h[j], lo.h[j]);
+      reinterpret_cast<uint4*>(Ws)[2 * row8] = hi.q;
+      reinterpret_cast<uint4*>(Ws)[2 * row8 + 1] = lo.q;
+      reinterpret_cast<uint4*>(Wsi)[(size_t)(k >> 3) * 2 * Vpad + v] = hi.q;
+      reinterpret_cast<uint4*>(Wsi)[(size_t)(k >> 3) * 2 * Vpad + Vpad + v] = lo.q;
+#pragma unroll
+      for (int j = 0; j < 8; j += 4)
+        reinterpret_cast<float4*>(Wi)[(size_t)((k + j) >> 2) * Vpad + v] =
+            make_float4(w[j], w[j + 1], w[j + 2], w[j + 3]);
+    }
+  }
+  if (lane == 0 && in) bias[v] = b_out ? b_out[v] : 0.f;
 }
 
 __global__ void k_fill_i32(int* p, long long n, int v) {
@@ -714,7 +750,7 @@ __device__ __forceinline__ void joiner_tile_small(const ModelDev& m, const JoinA
     }
   };
   load_w(0);
-  const float zscale = BF16 ? 1.f : m.zscale[0];
+  const float zscale = BF16 ? 1.f : m.zscale[col];
   const float bias = cvalid ? m.bias[col] : 0.f;
   // (rows of the tile's own slots: packing the active rows, as the larger tiles do, costs
   // this one more latency than the tiles it saves)
@@ -782,8 +818,8 @@ __device__ __forceinline__ void joiner_tile_small(const ModelDev& m, const JoinA
     const int row = 4 * lg + i;  // the 16 lanes of a DPP row share this row
     const f32x4* c = acc;
     const float zs = BF16 ? (c[0][i] + c[1][i]) + (c[2][i] + c[3][i])
-                          : (((c[1][i] + c[2][i]) + (c[NC - 2][i] + c[NC - 1][i])) +
-                             (c[0][i] + c[NC - 3][i])) * zscale;
+                          : unsplit(c[0][i] + c[NC - 3][i],
+                                    (c[1][i] + c[2][i]) + (c[NC - 2][i] + c[NC - 1][i]), zscale);
     const float z = cvalid ? zs + bias : -INFINITY;
     zr[i] = z;
     const float mx = row16_max(z);
@@ -903,12 +939,15 @@ __global__ __launch_bounds__(128 * WN, MBW == 2 ? 3 : 1) void k_joiner(ModelDev 
   const int Kpad = m.Kpad, V = m.V, Vpad = m.Vpad, nvt = a.nvt;
   const int vt = WN * ct + wc;  // this wave's vocabulary tile
   if (!joiner_tile_rows<NT, BM>(a, r0, s_row, s_wsum)) return;  // uniform: no row in this tile
-  // the epilogue's bias values, requested now so that their round trip is hidden
+  // the epilogue's bias and scale values, requested now so that their round trip is hidden
   // behind the main loop (clamped: past the vocabulary they are never used)
-  const float zscale = BF16 ? 1.f : m.zscale[0];
-  float bias_r[4];
+  float bias_r[4], zscale[4];
 #pragma unroll
-  for (int nb = 0; nb < 4; ++nb) bias_r[nb] = m.bias[min(64 * vt + 16 * nb + lr, V - 1)];
+  for (int nb = 0; nb < 4; ++nb) {
+    const int col = min(64 * vt + 16 * nb + lr, V - 1);
+    bias_r[nb] = m.bias[col];
+    zscale[nb] = BF16 ? 1.f : m.zscale[col];
+  }
 
   // slice loads: UA (h) and UB (W) chunks of 16 bytes per thread (BM and BN rows x 8 chunks)
   const char* hsrc = reinterpret_cast<const char*>(a.h);
@@ -1102,7 +1141,9 @@ __global__ __launch_bounds__(128 * WN, MBW == 2 ? 3 : 1) void k_joiner(ModelDev 
         float mx = -INFINITY;
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb) {
-          z[nb] = cvalid[nb] ? (BF16 ? acc[mb][nb][i] : (acc[mb][nb][i] + acc2[BF16 ? 0 : mb][nb][i]) * zscale) + bias[nb] : -INFINITY;
+          const float zs = BF16 ? acc[mb][nb][i]
+                                : unsplit(acc[mb][nb][i], acc2[BF16 ? 0 : mb][nb][i], zscale[nb]);
+          z[nb] = cvalid[nb] ? zs + bias[nb] : -INFINITY;
           mx = fmaxf(mx, z[nb]);
         }
         const float M = row16_max(mx);
@@ -1205,7 +1246,7 @@ __global__ __launch_bounds__(kSweepThreads) void k_joiner_sweep(ModelDev m, Join
       }
     }
   }
-  const float zscale = BF16 ? 1.f : m.zscale[0];
+  const float zscale = BF16 ? 1.f : m.zscale[min(col0, V - 1)];
   bool cvalid[NB];
   float bias[NB];
 #pragma unroll
@@ -1310,8 +1351,8 @@ __global__ __launch_bounds__(kSweepThreads) void k_joiner_sweep(ModelDev m, Join
         if constexpr (BF16)
           zs = acc[nb][0][i] + acc[nb][1][i];
         else
-          zs = (((acc[nb][1][i] + acc[nb][2][i]) + (acc[nb][4][i] + acc[nb][5][i])) +
-                (acc[nb][0][i] + acc[nb][3][i])) * zscale;
+          zs = unsplit(acc[nb][0][i] + acc[nb][3][i],
+                       (acc[nb][1][i] + acc[nb][2][i]) + (acc[nb][4][i] + acc[nb][5][i]), zscale);
         zr[nb][i] = cvalid[nb] ? zs + bias[nb] : -INFINITY;
         mx = fmaxf(mx, zr[nb][i]);
       }
@@ -3928,15 +3969,7 @@ hipError_t launch_model_setup(const float* embed, const float* conv, const float
                               const float* b_out, int V, int C, int Kpad, int Vpad, int bf16,
                               float* P0, float* P1, uint16_t* Ws, uint16_t* Wsi, float* zscale,
                               uint16_t* Wb, void* Wi, float* bias, hipStream_t st) {
-  if (!bf16) {
-    hipError_t e = launch_fill_i32(reinterpret_cast<int*>(zscale), 2, 0, st);
-    if (e != hipSuccess) return e;
-    const long long n = (long long)V * C;
-    hipLaunchKernelGGL(k_weight_max, dim3(grid_for(n, 2048, 512)), dim3(256), 0, st, w_out, n,
-                       reinterpret_cast<unsigned*>(zscale) + 1);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(k_model_setup, dim3(grid_for((long long)Vpad * Kpad, 256)), dim3(256), 0, st,
+  hipLaunchKernelGGL(k_model_setup, dim3((Vpad + 3) / 4), dim3(256), 0, st,
                      embed, conv, w_out, b_out, V, C, Kpad, Vpad, bf16, P0, P1, Ws, Wsi, zscale, Wb,
                      Wi, bias);
   return hipGetLastError();

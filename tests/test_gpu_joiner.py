@@ -117,25 +117,70 @@ def test_joiner_tilings(V, C, R, dtype):
     assert np.isfinite(got).all()
 
 
+def _logp64(m, enc, a, b):
+    """Log-probabilities in float64, the joiner input's tanh included."""
+    dec = np.maximum(m.conv[:, 0] * m.embed[a].astype(np.float64) + m.conv[:, 1] * m.embed[b], 0)
+    with np.errstate(over="ignore", invalid="ignore"):
+        z = np.tanh(enc + dec) @ m.w_out.astype(np.float64).T + m.b_out.astype(np.float64)
+    top = z.max(1, keepdims=True)
+    return z - (top + np.log(np.exp(z - top).sum(1, keepdims=True)))
+
+
+def _logp_gpu(m, enc, a, b, dtype="fp32"):
+    import torch
+    from paper_2211_00484_amd import tbs
+    model = tbs.Model.from_synth(m, dtype=dtype)
+    ctx = torch.from_numpy((a * m.vocab_size + b).astype(np.int32))
+    return tbs.joiner_logp(model, torch.from_numpy(enc).cuda(), ctx).cpu().numpy()
+
+
+# fp32 logits: tanh to 2e-7 absolute, operands and products to 2^-22, sums of C terms; per
+# unit of a label's own largest weight, as random signs add (the factor 3: worst of the rows)
+LOGIT_EPS = 3 * (2e-7 + 2.0 ** -22)
+
+# every tiling: small tiles, sweep, 64 x 128, and K beyond 512 in small and in large tiles
+RANGE_SHAPES = [(100, 64, 50), (500, 512, 40), (500, 512, 700), (700, 500, 9000), (300, 600, 40), (2000, 768, 2100)]
+
+
 @pytest.mark.parametrize("scale", [0.0, 1e-37, 1e-12, 1.0, 1e6, 1e30])
 @pytest.mark.parametrize("V,C,R", [(100, 64, 50), (100, 64, 2600), (700, 64, 3000), (300, 600, 40)])
 def test_joiner_weight_scales(scale, V, C, R):
-    """fp32 weights of any magnitude, rows 2^0 ... 2^-30 below the largest: the logits keep
-    fp32's accuracy relative to their products (bias 0, so log-probabilities show them)."""
-    import torch
-    from paper_2211_00484_amd import tbs
+    """fp32 weights of any magnitude, rows 2^0 ... 2^-30 of the largest: finite, and right to
+    fp32's accuracy in each label's logit and in the normaliser (which the largest labels
+    set; what the small labels keep beside large ones is test_joiner_weight_range's)."""
     rng = np.random.default_rng(3)
     m = synth.make_model(rng, V, C, 1.0)
     m.w_out *= (np.float32(scale) * 2.0 ** -rng.integers(0, 31, size=(V, 1))).astype(np.float32)
     m.b_out[:] = 0
     enc = rng.standard_normal((R, C), dtype=np.float32)
     a, b = rng.integers(0, V, R), rng.integers(0, V, R)
-    model = tbs.Model.from_synth(m)
-    got = tbs.joiner_logp(model, torch.from_numpy(enc).cuda(),
-                          torch.from_numpy((a * V + b).astype(np.int32))).cpu().numpy()
-    dec = np.maximum(m.conv[:, 0] * m.embed[a].astype(np.float64) + m.conv[:, 1] * m.embed[b], 0)
-    z = np.tanh(enc + dec) @ m.w_out.astype(np.float64).T
-    want = z - (z.max(1, keepdims=True) + np.log(np.exp(z - z.max(1, keepdims=True)).sum(1, keepdims=True)))
-    # tanh to 2e-7 absolute, products to 2^-22, sums of C terms of the largest weights
-    tol = 1e-6 + 1e-6 * np.sqrt(C) * np.abs(m.w_out).max() + 2e-7 * np.abs(want)
+    got, want = _logp_gpu(m, enc, a, b), _logp64(m, enc, a, b)
+    eps = LOGIT_EPS * np.sqrt(C) * np.abs(m.w_out).max(1)
+    tol = 1e-6 + 2e-7 * np.abs(want) + eps + (np.exp(want) * eps).sum(1, keepdims=True)
     assert (np.abs(got - want) <= tol).all()
+
+
+@pytest.mark.parametrize("p", [0, 20, 24, 27])
+@pytest.mark.parametrize("where", ["row", "column"])
+@pytest.mark.parametrize("V,C,R", RANGE_SHAPES)
+def test_joiner_weight_range(V, C, R, where, p):
+    """Weights 2^p above the others that no other label's result depends on: a label's row,
+    the label masked by its bias, or the column of a unit whose input is 0.  The others keep
+    fp32's accuracy."""
+    rng = np.random.default_rng(V + C)
+    m = synth.make_model(rng, V, C, 0.05)
+    enc = rng.standard_normal((R, C), dtype=np.float32)
+    a, b = rng.integers(0, V, R), rng.integers(0, V, R)
+    own = np.abs(m.w_out).max()
+    if where == "row":
+        m.w_out[3] *= np.float32(2.0 ** p)
+        m.b_out[3] = -1e30
+    else:
+        m.w_out[:, 7] = np.float32(0.05 * 2.0 ** p)
+        m.embed[:, 7] = 0
+        enc[:, 7] = 0
+    got, want = _logp_gpu(m, enc, a, b), _logp64(m, enc, a, b)
+    keep = np.arange(V) != (3 if where == "row" else -1)
+    err = np.abs(got - want)[:, keep].max()
+    say(f"  {where} 2^{p}: max |dlogp| = {err:.3g}")
+    assert err <= 2e-7 * np.abs(want[:, keep]).max() + 2 * LOGIT_EPS * np.sqrt(C) * own
