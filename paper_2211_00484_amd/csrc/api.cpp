@@ -805,30 +805,29 @@ tbs_status tbs_model_create(int32_t vocab_size, int32_t dim, int32_t context_siz
   if (e == hipSuccess)
     e = hipDeviceGetAttribute(&m->coop, hipDeviceAttributeCooperativeLaunch, m->dev);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&m->busy, hipEventDisableTiming);
-  // The tables: one allocation when any of them is large (a hipMalloc of 2 MiB or more
-  // takes some 25 us, a smaller one about 1 us), else one each.
+  // The tables, in few allocations: a hipMalloc of 2 MiB or more takes some 25 us whatever
+  // its size, a smaller one about 1 us.  One for all of them when any is that large, else
+  // each takes as many as stay below it.
   {
     const size_t wb = m->bf16 ? 2 : 4;  // bytes per packed weight (an fp16 pair: 4)
     const size_t sizes[7] = {VK * 4, VK * 4, VpK * wb, m->bf16 ? 0 : VpK * wb, VpK * wb,
                              (size_t)m->V * 4, m->bf16 ? 0 : (size_t)m->Vpad * 4};
+    const size_t big = 2u << 20;
+    auto room = [](size_t n) { return (n + 255) / 256 * 256; };
+    size_t largest = 0;
+    for (size_t n : sizes) largest = std::max(largest, room(n));
     char* at[7] = {};
-    size_t total = 0, largest = 0;
-    for (size_t n : sizes) {
-      total += (n + 255) / 256 * 256;
-      largest = std::max(largest, n);
-    }
-    char* next = nullptr;
-    if (largest >= (2u << 20)) {
-      if (e == hipSuccess) e = dalloc(&next, total);
-      if (e == hipSuccess) m->tables.push_back(next);
-    }
-    for (int i = 0; i < 7 && e == hipSuccess; ++i) {
-      if (next) {
-        at[i] = next;
-        next += (sizes[i] + 255) / 256 * 256;
-      } else if (sizes[i]) {
-        e = dalloc(&at[i], sizes[i]);
-        if (e == hipSuccess) m->tables.push_back(at[i]);
+    for (int i = 0, j; i < 7 && e == hipSuccess; i = j) {
+      size_t total = 0;
+      for (j = i; j < 7 && (j == i || largest >= big || total + room(sizes[j]) < big); ++j)
+        total += room(sizes[j]);
+      char* next = nullptr;
+      e = dalloc(&next, total);
+      if (e != hipSuccess) break;
+      m->tables.push_back(next);
+      for (int k = i; k < j; ++k) {
+        at[k] = next;
+        next += room(sizes[k]);
       }
     }
     m->P0 = (float*)at[0];
