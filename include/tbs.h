@@ -97,7 +97,11 @@ typedef enum { TBS_JOINER_FP32 = 0, TBS_JOINER_BF16 = 1 } tbs_joiner_dtype;
  *   (TBS_EUNSUPPORTED otherwise).
  *   embed  DEVICE float [V][C];  conv DEVICE float [C][2];
  *   w_out  DEVICE float [V][C] (torch Linear layout);  b_out DEVICE float [V] or NULL (= 0).
- *   dtype  TBS_JOINER_FP32: fp32 operands; TBS_JOINER_BF16: tanh output and
+ *   dtype  TBS_JOINER_FP32: fp32 operands (whole batches may be multiplied as pairs of
+ *          fp16 that carry 23 of their 24 bits, with errors against 64 bits no larger
+ *          than fp32 products'; C below 96, weights that are not finite, and rows of
+ *          w_out most of whose weights are more than 2^28 below the row's largest keep
+ *          fp32 products); TBS_JOINER_BF16: tanh output and
  *          w_out rounded to bfloat16 (nearest, ties to even), fp32 accumulation.
  * The library copies what it needs (and precomputes conv-tap-scaled embedding
  * tables) on hip_stream and synchronises that stream before returning, so the

@@ -49,6 +49,33 @@ tbs_status hip_fail(hipError_t e, const char* what) {
     if (e_ != hipSuccess) return hip_fail(e_, what); \
   } while (0)
 
+// Pinned host words that kernels report to, one per model being created; kept for the next
+// (a copy back from device memory takes some 8 us more).
+std::mutex g_wordmu;
+std::vector<int*> g_words;
+
+hipError_t host_word_take(int** w) {
+  *w = nullptr;
+  {
+    std::lock_guard<std::mutex> lk(g_wordmu);
+    if (!g_words.empty()) {
+      *w = g_words.back();
+      g_words.pop_back();
+    }
+  }
+  if (!*w) {
+    const hipError_t e = hipHostMalloc((void**)w, sizeof(int), hipHostMallocPortable);
+    if (e != hipSuccess) return e;
+  }
+  **w = 0;
+  return hipSuccess;
+}
+
+void host_word_return(int* w) {
+  std::lock_guard<std::mutex> lk(g_wordmu);
+  g_words.push_back(w);
+}
+
 template <class T>
 hipError_t dalloc(T** p, size_t n) {
   *p = nullptr;
@@ -169,6 +196,7 @@ std::atomic<unsigned> g_wrap{0};
 
 struct tbs_model {
   int V = 0, C = 0, Kpad = 0, Vpad = 0, bf16 = 0;
+  int direct = 0;  // fp32 products in the frame joiner (ModelDev::direct)
   int dev = 0, ncu = 0, coop = 0;   // device, compute units, cooperative launch support
   XBuf xbuf;
   unsigned spin_limit = kDefaultSpinLimit;  // polls before a grouped-kernel wait gives up
@@ -224,6 +252,7 @@ ModelDev model_dev(const tbs_model* m) {
   d.Kpad = m->Kpad;
   d.Vpad = m->Vpad;
   d.bf16 = m->bf16;
+  d.direct = m->direct;
   d.P0 = m->P0;
   d.P1 = m->P1;
   d.Ws = m->Ws;
@@ -546,7 +575,7 @@ tbs_status enqueue_frames(tbs_model* m, const GraphDev& gd, float beam,
                    [&] { return launch_stream(md, gd, d, beam, trace, splan, st); }),
             "launch(stream)");
   if (!per_stream) {
-    const JoinerPlan plan = plan_joiner(d.B * d.Nc, m->Vpad, m->Kpad, m->bf16, m->ncu, d.KT > 0);
+    const JoinerPlan plan = plan_joiner(md, d.B * d.Nc, m->ncu, d.KT > 0);
     auto frames = [&](hipStream_t s2) -> hipError_t {
       for (int t = 0; t < maxlen; ++t) {
         hipError_t e = launch(TBS_KERNEL_JOINER,
@@ -799,6 +828,8 @@ tbs_status tbs_model_create(int32_t vocab_size, int32_t dim, int32_t context_siz
   m->Vpad = round_up(vocab_size, kJoinerBN);
   m->bf16 = dtype == TBS_JOINER_BF16;
   const size_t VK = (size_t)m->V * m->Kpad, VpK = (size_t)m->Vpad * m->Kpad;
+  const bool pairs_fit = !m->bf16 && m->C >= kPairsMinC;  // unless the weights do not
+  int* wide = nullptr;  // set by the setup kernel
   hipError_t e = hipGetDevice(&m->dev);
   if (e == hipSuccess)
     e = hipDeviceGetAttribute(&m->ncu, hipDeviceAttributeMultiprocessorCount, m->dev);
@@ -810,8 +841,9 @@ tbs_status tbs_model_create(int32_t vocab_size, int32_t dim, int32_t context_siz
   // each takes as many as stay below it.
   {
     const size_t wb = m->bf16 ? 2 : 4;  // bytes per packed weight (an fp16 pair: 4)
-    const size_t sizes[7] = {VK * 4, VK * 4, VpK * wb, m->bf16 ? 0 : VpK * wb, VpK * wb,
-                             (size_t)m->V * 4, m->bf16 ? 0 : (size_t)m->Vpad * 4};
+    const size_t pairs = pairs_fit ? 1 : 0;
+    const size_t sizes[7] = {VK * 4, VK * 4, m->bf16 ? VpK * wb : pairs * VpK * wb, pairs * VpK * wb,
+                             VpK * wb, (size_t)m->V * 4, pairs * m->Vpad * 4};
     const size_t big = 2u << 20;
     auto room = [](size_t n) { return (n + 255) / 256 * 256; };
     size_t largest = 0;
@@ -832,16 +864,23 @@ tbs_status tbs_model_create(int32_t vocab_size, int32_t dim, int32_t context_siz
     }
     m->P0 = (float*)at[0];
     m->P1 = (float*)at[1];
-    (m->bf16 ? m->Wb : m->Ws) = (uint16_t*)at[2];
-    m->Wsi = m->bf16 ? nullptr : (uint16_t*)at[3];
+    if (m->bf16) m->Wb = (uint16_t*)at[2];
+    if (pairs_fit) {
+      m->Ws = (uint16_t*)at[2];
+      m->Wsi = (uint16_t*)at[3];
+      m->zscale = (float*)at[6];
+    }
     m->Wi = at[4];
     m->bias = (float*)at[5];
-    m->zscale = (float*)at[6];
   }
+  if (e == hipSuccess && pairs_fit) e = host_word_take(&wide);
   if (e == hipSuccess)
     e = launch_model_setup(embed, conv, w_out, b_out, m->V, m->C, m->Kpad, m->Vpad, m->bf16,
-                           m->P0, m->P1, m->Ws, m->Wsi, m->zscale, m->Wb, m->Wi, m->bias, st);
+                           m->P0, m->P1, m->Ws, m->Wsi, m->zscale, wide, m->Wb, m->Wi, m->bias, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
+  const bool fit = pairs_fit && wide && *wide == 0;
+  if (wide && e == hipSuccess) host_word_return(wide);  // (the kernel is done with it)
+  m->direct = m->bf16 || fit ? 0 : round_up(m->C, 16);
   if (e != hipSuccess) {
     tbs_model_destroy(m);
     return hip_fail(e, "tbs_model_create");

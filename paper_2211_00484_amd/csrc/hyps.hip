@@ -107,7 +107,7 @@ __device__ __forceinline__ bool cand_before(const Cand& x, const Cand& y) {
 }
 
 // Joiner rows of stream b's nh hypotheses, row b * N + r: h = tanh(enc + ReLU(P0[a] + P1[c]))
-// for context (a, c) of ctx[r], as fp16 pairs or bf16 (RNE).  (Hypotheses with equal contexts
+// for context (a, c) of ctx[r], as fp16 pairs, fp32 or bf16 (RNE).  (Hypotheses with equal contexts
 // get equal rows.)  Column quads when C is a multiple of 4, kBatch of them per thread with
 // all their table loads in flight together.  enc, ctx: LDS.
 template <int NT>
@@ -151,13 +151,12 @@ __device__ void hyp_rows(const ModelDev& m, const HypDev& d, int b, int nh, cons
               make_uint2((unsigned)f32_to_bf16_rne(h0) | (unsigned)f32_to_bf16_rne(h1) << 16,
                          (unsigned)f32_to_bf16_rne(h2) | (unsigned)f32_to_bf16_rne(h3) << 16);
         } else {
-          uint4 v;
-          split_pair(h0, h1, v.x, v.z);
-          split_pair(h2, h3, v.y, v.w);
-          *reinterpret_cast<uint4*>(reinterpret_cast<unsigned*>(d.h) + o) = v;
+          *reinterpret_cast<uint4*>(reinterpret_cast<unsigned*>(d.h) + o) = h_quad(m.direct, h0, h1, h2, h3);
         }
       } else if (m.bf16) {
         reinterpret_cast<uint16_t*>(d.h)[o] = f32_to_bf16_rne(h0);
+      } else if (m.direct) {
+        reinterpret_cast<float*>(d.h)[o] = h0;
       } else {
         store_split(d.h, o - k[u], k[u], h0);
       }

@@ -46,16 +46,22 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
 // low x high, summed apart and scaled by 2^-12; low x low is below 2^-22 of it).
 // Rows of h hold four values in 16 bytes (their high parts, then their low parts), W eight
 // in 32.
+// fp32 products instead (ModelDev::direct):
+//  - for C < kPairsMinC: the pairs' rounding is then no longer hidden in the sums' (errors
+//    against 64 bits, V = 100, 2,000 rows: C = 32 3.24e-8 by pairs, 3.14e-8 by fp32; C = 96
+//    3.85e-8 and 3.87e-8, and apart from there on: C = 384 7.3e-8 and 8.4e-8);
+//  - for models whose weights the pairs do not hold: a number that is not finite, or a row
+//    most of whose weights are more than 2^28 below its largest (which then belong to units
+//    that may be 0).
+constexpr int kPairsMinC = 96;
 constexpr float kHScale = 16384.f, kLowScale = 4096.f;
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint16_t f16_bits(_Float16 x) { return __builtin_bit_cast(uint16_t, x); }
-// (an infinite or NaN x keeps it in the high part)
 __device__ __forceinline__ void f32_split(float x, uint16_t& hi, uint16_t& lo) {
   const _Float16 a = (_Float16)x;
-  const float r = (x - (float)a) * kLowScale;
   hi = f16_bits(a);
-  lo = f16_bits((_Float16)(fabsf(r) < INFINITY ? r : 0.f));
+  lo = f16_bits((_Float16)((x - (float)a) * kLowScale));
 }
 // h (finite, |h| <= 1) as element k of the row at element row0 of base
 __device__ __forceinline__ void store_split(void* base, size_t row0, int k, float h) {
@@ -71,6 +77,14 @@ __device__ __forceinline__ void split_pair(float h0, float h1, unsigned& hi, uns
   const f32x2 r = {(x[0] - (float)a[0]) * kLowScale, (x[1] - (float)a[1]) * kLowScale};
   hi = __builtin_bit_cast(unsigned, a);
   lo = __builtin_bit_cast(unsigned, __builtin_convertvector(r, f16x2));
+}
+// Four elements of a row of h as an fp32 model holds them.
+__device__ __forceinline__ uint4 h_quad(int direct, float h0, float h1, float h2, float h3) {
+  uint4 v;
+  split_pair(h0, h1, v.x, v.z);
+  split_pair(h2, h3, v.y, v.w);
+  if (direct) v = make_uint4(__float_as_uint(h0), __float_as_uint(h1), __float_as_uint(h2), __float_as_uint(h3));
+  return v;
 }
 // The logit's products from their two sums, zscale the row's inverse scale.
 __device__ __forceinline__ float unsplit(float high, float cross, float zscale) {
@@ -89,9 +103,10 @@ __device__ __forceinline__ float tanh_fast(float x) {
 struct ModelDev {
   int V, C, Kpad, Vpad;
   int bf16;
+  int direct;               // fp32 products in the frame joiner: K to sum (C rounded up to 16), else 0
   const float* P0;          // [V][Kpad] conv tap 0 * embedding (older label)
   const float* P1;          // [V][Kpad] conv tap 1 * embedding (newer label)
-  const uint16_t* Ws;       // [Vpad][Kpad] joiner weight as fp16 pairs (fp32 mode)
+  const uint16_t* Ws;       // [Vpad][Kpad] joiner weight as fp16 pairs (fp32 mode, unless direct)
   const uint16_t* Wsi;      // [Kpad/8][2][Vpad][8] the same, high and low parts interleaved
                             // by 16-byte k slices (small frame-joiner tiles)
   const float* zscale;      // [Vpad]: logit = zscale * (sum of products of scaled pairs)
@@ -128,7 +143,7 @@ struct DecodeDev {
   int* nctx;                // [B]
   int* ctx_list;            // [B][Nc], ascending
   double* offset;           // [B]
-  void* h;                  // [B*Nc][Kpad] joiner input rows tanh(enc + dec) (fp16 pairs or bf16)
+  void* h;                  // [B*Nc][Kpad] joiner input rows tanh(enc + dec) (fp16 pairs, bf16; direct: fp32)
   float* logits;            // [B*Nc][Vpad] (general graphs)
   float2* stats;            // [B*Nc][nvt]: (max, sum exp(z - max)) per vocabulary tile
   float* tk_z;              // [B*Nc][nvt*4][KT] trivial fast path: best logits per 16-column sub-tile
@@ -140,7 +155,7 @@ struct DecodeDev {
 };
 
 struct JoinerPlan {
-  bool small;               // 16 x 64 tiles
+  bool small;               // 16 x 64 tiles (direct models: always)
   bool sweep;               // sweep (n_ct column tiles x n_rt row groups); else GEMM tiles (shape)
   int shape;                // GEMM tiles: 0 = 64 x 128, 1 = 256 x 256 (bf16)
   int n_rt, n_ct;           // row and column tiles
@@ -149,7 +164,7 @@ struct JoinerPlan {
 };
 
 // topk: the joiner writes each row's best labels (trivial graph) instead of logits
-JoinerPlan plan_joiner(int rows, int Vpad, int Kpad, int bf16, int ncu, bool topk = false);
+JoinerPlan plan_joiner(const ModelDev& m, int rows, int ncu, bool topk = false);
 
 // Events for the next non-cooperative kernel launch of the calling thread, recorded in
 // that launch's dispatch packet (per-kernel profiling); pending until a launch takes them.
@@ -184,7 +199,7 @@ hipError_t launch_stream(const ModelDev& m, const GraphDev& g, const DecodeDev& 
 hipError_t launch_model_setup(const float* embed, const float* conv, const float* w_out,
                               const float* b_out, int V, int C, int Kpad, int Vpad, int bf16,
                               float* P0, float* P1, uint16_t* Ws, uint16_t* Wsi, float* zscale,
-                              uint16_t* Wb, void* Wi, float* bias, hipStream_t st);
+                              int* wide, uint16_t* Wb, void* Wi, float* bias, hipStream_t st);
 hipError_t launch_fill_i32(int* p, long long n, int v, hipStream_t st);
 // out[b] = min(max(in[b], 0), T) for b < B (device arrays)
 hipError_t launch_clamp_lengths(const int* in, int* out, int B, int T, hipStream_t st);

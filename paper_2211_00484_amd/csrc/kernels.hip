@@ -232,16 +232,17 @@ __device__ __forceinline__ void load8(const float* __restrict__ row, int k, int 
     }
 }
 
-// One wave per vocabulary row, eight columns per lane and step.
+// One wave per vocabulary row, eight columns per lane and step.  Ws (fp32 models that may
+// use pairs): also *wide = 1 (host memory, 0 before) if a row is not for
+// pairs.
 __global__ __launch_bounds__(256) void k_model_setup(
     const float* __restrict__ E, const float* __restrict__ conv, const float* __restrict__ W,
     const float* __restrict__ b_out, int V, int C, int Kpad, int Vpad, int bf16,
     float* __restrict__ P0, float* __restrict__ P1, uint16_t* __restrict__ Ws,
-    uint16_t* __restrict__ Wsi, float* __restrict__ zscale, uint16_t* __restrict__ Wb,
-    void* __restrict__ Wi, float* __restrict__ bias) {
+    uint16_t* __restrict__ Wsi, float* __restrict__ zscale, int* __restrict__ wide,
+    uint16_t* __restrict__ Wb, void* __restrict__ Wi, float* __restrict__ bias) {
   const int lane = threadIdx.x & 63, v = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (v >= Vpad) return;  // whole wave
-  const bool in = v < V;
+  const bool in = v < V;  // (Vpad is a multiple of 4)
   const int Cv = in ? C : 0;  // rows past the vocabulary are zeros
   const float* w_row = W + (size_t)(in ? v : 0) * C;
   const float* e_row = E + (size_t)(in ? v : 0) * C;
@@ -249,8 +250,8 @@ __global__ __launch_bounds__(256) void k_model_setup(
                    ((reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(E) |
                      reinterpret_cast<uintptr_t>(conv)) & 15) == 0;
   int sexp = 0;
-  if (!bf16) {
-    unsigned wmax = 0;  // largest finite magnitude
+  if (Ws) {
+    unsigned wmax = 0, nonzero = 0, small = 0, odd = 0;  // largest finite magnitude; counts
     for (int k = 8 * lane; k < Cv; k += 512) {
       float w[8];
       load8(w_row, k, Cv, vec, w);
@@ -260,8 +261,26 @@ __global__ __launch_bounds__(256) void k_model_setup(
         if (u < 0x7f800000u) wmax = max(wmax, u);
       }
     }
-    sexp = split_exponent(wave_max_u32(wmax));
+    wmax = wave_max_u32(wmax);
+    sexp = split_exponent(wmax);
+    // weights that pairs at this row's scale would cut short, and ones that are no number
+    const float limit = __uint_as_float(wmax) * 0x1p-28f;
+    for (int k = 8 * lane; k < Cv; k += 512) {
+      float w[8];
+      load8(w_row, k, Cv, vec, w);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        nonzero += w[j] != 0.f;
+        small += w[j] != 0.f && fabsf(w[j]) < limit;
+        odd += !(fabsf(w[j]) < INFINITY);
+      }
+    }
+    // (the last lane holds the sums)
+    nonzero = wave_incl_scan_u32(nonzero);
+    small = wave_incl_scan_u32(small);
+    const bool bad = wave_max_u32(odd) != 0 || (lane == 63 && 2 * small > nonzero);
     if (lane == 0) zscale[v] = ldexpf(1.f / kHScale, -sexp);
+    if (bad) *wide = 1;
   }
   for (int k = 8 * lane; k < Kpad; k += 512) {
     float w[8], e[8];
@@ -292,12 +311,14 @@ __global__ __launch_bounds__(256) void k_model_setup(
       reinterpret_cast<uint4*>(Wb)[row8] = hi.q;
       reinterpret_cast<uint4*>(Wi)[col8] = hi.q;
     } else {
+      if (Ws) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) f32_split(ldexpf(w[j], sexp), hi.h[j], lo.h[j]);
-      reinterpret_cast<uint4*>(Ws)[2 * row8] = hi.q;
-      reinterpret_cast<uint4*>(Ws)[2 * row8 + 1] = lo.q;
-      reinterpret_cast<uint4*>(Wsi)[(size_t)(k >> 3) * 2 * Vpad + v] = hi.q;
-      reinterpret_cast<uint4*>(Wsi)[(size_t)(k >> 3) * 2 * Vpad + Vpad + v] = lo.q;
+        for (int j = 0; j < 8; ++j) f32_split(ldexpf(w[j], sexp), hi.h[j], lo.h[j]);
+        reinterpret_cast<uint4*>(Ws)[2 * row8] = hi.q;
+        reinterpret_cast<uint4*>(Ws)[2 * row8 + 1] = lo.q;
+        reinterpret_cast<uint4*>(Wsi)[(size_t)(k >> 3) * 2 * Vpad + v] = hi.q;
+        reinterpret_cast<uint4*>(Wsi)[(size_t)(k >> 3) * 2 * Vpad + Vpad + v] = lo.q;
+      }
 #pragma unroll
       for (int j = 0; j < 8; j += 4)
         reinterpret_cast<float4*>(Wi)[(size_t)((k + j) >> 2) * Vpad + v] =
@@ -330,7 +351,7 @@ __global__ void k_clamp_lengths(const int* __restrict__ in, int* __restrict__ ou
 // row enc_rows + r * enc_stride (enc_stride = 0: one shared frame).
 // Thread tid owns columns tid, tid + NT, ... of every row (Kpad is a multiple of
 // 512); a batch's loads are all issued before any tanh.
-// SPLIT: fp16 pairs in place of fp32 (rows of the frame schedule)
+// SPLIT: fp16 pairs in place of fp32 unless the model is direct (rows of the frame schedule)
 template <int NT, bool SPLIT, int U = 16>  // U: (row, column) elements per thread per batch
 __device__ void write_h_rows(const ModelDev& m, const float* __restrict__ enc_rows,
                              long long enc_stride, const int2* rowoff, int nrows,
@@ -373,7 +394,7 @@ __device__ void write_h_rows(const ModelDev& m, const float* __restrict__ enc_ro
       const size_t o = (size_t)ro[u] * hstride + k;
       if (m.bf16)
         reinterpret_cast<uint16_t*>(hbase)[o] = f32_to_bf16_rne(h);
-      else if (SPLIT)
+      else if (SPLIT && !m.direct)
         store_split(hbase, (size_t)ro[u] * hstride, k, h);
       else
         reinterpret_cast<float*>(hbase)[o] = h;
@@ -384,8 +405,8 @@ __device__ void write_h_rows(const ModelDev& m, const float* __restrict__ enc_ro
 // The same rows for C a multiple of 4, four adjacent columns per item: item i of the
 // nrows x Kpad / 4 (row, column quad) items is thread i mod NT's; a batch of U items per
 // thread issues U 16-byte loads of P0 and of P1 (all in flight at once), then U 8-byte (bf16)
-// or 16-byte (fp16 pairs) stores.  enc is one frame shared by every row.  (Rows of the
-// frame schedule: never fp32.)
+// or 16-byte (fp16 pairs, fp32) stores.  enc is one frame shared by every row.  (Rows of the
+// frame schedule: fp32 in direct models only.)
 template <int NT, int U>
 __device__ void write_h_rows_quads(const ModelDev& m, const float* __restrict__ enc,
                                    const int2* rowoff, int nrows, void* __restrict__ hbase,
@@ -439,12 +460,8 @@ __device__ void write_h_rows_quads(const ModelDev& m, const float* __restrict__ 
 #pragma unroll
       for (int u = 0; u < U; ++u)
         if (i0 + tid + u * NT < total)
-        {
-          uint4 v;
-          split_pair(h[u].x, h[u].y, v.x, v.z);
-          split_pair(h[u].z, h[u].w, v.y, v.w);
-          *reinterpret_cast<uint4*>(reinterpret_cast<unsigned*>(hbase) + (size_t)ro[u] * hstride + ko[u]) = v;
-        }
+          *reinterpret_cast<uint4*>(reinterpret_cast<unsigned*>(hbase) + (size_t)ro[u] * hstride + ko[u]) =
+              h_quad(m.direct, h[u].x, h[u].y, h[u].z, h[u].w);
     }
   }
 }
@@ -452,7 +469,7 @@ __device__ void write_h_rows_quads(const ModelDev& m, const float* __restrict__ 
 // The same rows for an even C, two adjacent columns per item: thread tid owns the
 // column pairs (2 tid, 2 tid + 1), (2 tid + 2 NT, ...), ... of every row, so a batch
 // of U items issues U 8-byte loads of P0 and of P1 (all in flight at once) and U 4-byte
-// (bf16) or 2 U 4-byte (fp16 pairs) stores.  enc is one frame shared by every row.
+// (bf16) or 2 U 4-byte (fp16 pairs, fp32) stores.  enc is one frame shared by every row.
 template <int NT, int U = 16>
 __device__ void write_h_rows_pairs(const ModelDev& m, const float* __restrict__ enc,
                                    const int2* rowoff, int nrows, void* __restrict__ hbase,
@@ -509,11 +526,16 @@ __device__ void write_h_rows_pairs(const ModelDev& m, const float* __restrict__ 
     } else {
 #pragma unroll
       for (int u = 0; u < U; ++u)
-        if (ro[u] < nrows)
-        {
+        if (ro[u] < nrows) {
           const float2 h = hpair(u);
-          unsigned* quad = reinterpret_cast<unsigned*>(hbase) + (size_t)ro[u] * hstride + (ko[u] & ~3) + ((ko[u] >> 1) & 1);
-          split_pair(h.x, h.y, quad[0], quad[2]);
+          unsigned hi, lo;
+          split_pair(h.x, h.y, hi, lo);
+          // a pair of columns: words 0 and 2, or 1 and 3, of its quad (fp32: its own two)
+          const int first = (ko[u] >> 1) & 1, step = m.direct ? 1 : 2;
+          unsigned* quad = reinterpret_cast<unsigned*>(hbase) + (size_t)ro[u] * hstride + (ko[u] & ~3) +
+                           (m.direct ? 2 * first : first);
+          quad[0] = m.direct ? __float_as_uint(h.x) : hi;
+          quad[step] = m.direct ? __float_as_uint(h.y) : lo;
         }
     }
   }
@@ -562,10 +584,7 @@ __global__ __launch_bounds__(256) void k_h_rows(ModelDev m, const float* __restr
           make_uint2((unsigned)f32_to_bf16_rne(h0) | ((unsigned)f32_to_bf16_rne(h1) << 16),
                      (unsigned)f32_to_bf16_rne(h2) | ((unsigned)f32_to_bf16_rne(h3) << 16));
     } else {
-      uint4 v;
-      split_pair(h0, h1, v.x, v.z);
-      split_pair(h2, h3, v.y, v.w);
-      *reinterpret_cast<uint4*>(reinterpret_cast<unsigned*>(h) + o) = v;
+      *reinterpret_cast<uint4*>(reinterpret_cast<unsigned*>(h) + o) = h_quad(m.direct, h0, h1, h2, h3);
     }
   }
 }
@@ -690,19 +709,86 @@ struct JoinShared {
   float m[4][16], s[4][16];
 };
 
+// Epilogue of a small tile: zs are the lane's products for rows 4 lg + i of the tile, without
+// the bias of its column.
+template <bool TOPK>
+__device__ __forceinline__ void joiner_small_epilogue(const ModelDev& m, const JoinArgs& a, int ct,
+                                                      JoinShared& js, const float (&zs)[4], float bias) {
+  const int* s_row = js.row;
+  float(*s_m)[16] = js.m;
+  float(*s_s)[16] = js.s;
+  constexpr int BM = 16;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lr = lane & 15, lg = lane >> 4, nvt = a.n_ct;
+  const int col = ct * kJoinerBN + 16 * wave + lr;
+  const bool cvalid = col < m.V;
+  // epilogue.  First everything that needs the workgroup barrier (per-row max
+  // and sum exp over the tile, combined across the 4 waves in LDS); the global
+  // stores come after it, so the barrier never waits on them.
+  float zr[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = 4 * lg + i;  // the 16 lanes of a DPP row share this row
+    const float z = cvalid ? zs[i] + bias : -INFINITY;
+    zr[i] = z;
+    const float mx = row16_max(z);
+    const float e = row16_sum(cvalid ? expf(z - mx) : 0.f);
+    if (lr == 0) {
+      s_m[wave][row] = mx;
+      s_s[wave][row] = e;
+    }
+  }
+  __syncthreads();
+  if (tid < BM && s_row[tid] >= 0) {
+    float M = s_m[0][tid];
+    for (int w = 1; w < 4; ++w) M = fmaxf(M, s_m[w][tid]);
+    float S = 0.f;
+    for (int w = 0; w < 4; ++w) S += s_s[w][tid] == 0.f ? 0.f : s_s[w][tid] * expf(s_m[w][tid] - M);
+    a.stats[(size_t)s_row[tid] * nvt + ct] = make_float2(M, S);
+  }
+  // logits (general graphs) or each row's best KT labels per 16-column sub-tile
+  // (trivial graph), found with DPP row reductions
+  const int nsub = nvt * (kJoinerBN / 16);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = s_row[4 * lg + i];
+    const float z = zr[i];
+    const bool act = row >= 0;
+    if (!TOPK) {
+      if (act && cvalid) a.logits[(size_t)row * (nvt * kJoinerBN) + col] = z;
+    } else {
+      unsigned long long key = (cvalid && col >= 1)
+                                   ? ((unsigned long long)f2ord(z) << 32) | (0xffffffffu - (unsigned)col)
+                                   : 0ull;
+      const size_t ob = ((size_t)max(row, 0) * nsub + ct * (kJoinerBN / 16) + wave) * a.KT;
+      for (int q = 0; q < a.KT; ++q) {
+        const unsigned long long best = row16_max_u64(key);
+        if (act && best != 0ull && key == best) {
+          a.tk_z[ob + q] = z;
+          a.tk_c[ob + q] = col;
+        }
+        if (act && best == 0ull && lr == 0) {
+          a.tk_z[ob + q] = -INFINITY;
+          a.tk_c[ob + q] = -1;
+        }
+        if (key == best) key = 0ull;
+      }
+      if (act && ct == 0 && wave == 0 && lr == 0) a.z0[row] = z;
+    }
+  }
+}
+
 // One joiner tile of frame a.t.  Uniform
 // across the workgroup; a tile without active rows computes nothing.
 template <bool BF16, bool TOPK>
 __device__ __forceinline__ void joiner_tile_small(const ModelDev& m, const JoinArgs& a, int ct, int rt,
                                             unsigned char* smem, JoinShared& js) {
   int* s_row = js.row;
-  float(*s_m)[16] = js.m;
-  float(*s_s)[16] = js.s;
   constexpr int BM = 16;
   constexpr int ESZ = BF16 ? 2 : 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r0 = rt * BM, n0 = ct * kJoinerBN;
-  const int Kpad = m.Kpad, V = m.V, nvt = a.n_ct;
+  const int Kpad = m.Kpad, V = m.V;
   const int lr = lane & 15, lg = lane >> 4;
   const int col = n0 + 16 * wave + lr;
   const bool cvalid = col < V;
@@ -809,64 +895,83 @@ __device__ __forceinline__ void joiner_tile_small(const ModelDev& m, const JoinA
     }
   }
 
-  // epilogue.  First everything that needs the workgroup barrier (per-row max
-  // and sum exp over the tile, combined across the 4 waves in LDS); the global
-  // stores come after it, so the barrier never waits on them.
-  float zr[4];
+  float zs[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int row = 4 * lg + i;  // the 16 lanes of a DPP row share this row
     const f32x4* c = acc;
-    const float zs = BF16 ? (c[0][i] + c[1][i]) + (c[2][i] + c[3][i])
-                          : unsplit(c[0][i] + c[NC - 3][i],
-                                    (c[1][i] + c[2][i]) + (c[NC - 2][i] + c[NC - 1][i]), zscale);
-    const float z = cvalid ? zs + bias : -INFINITY;
-    zr[i] = z;
-    const float mx = row16_max(z);
-    const float e = row16_sum(cvalid ? expf(z - mx) : 0.f);
-    if (lr == 0) {
-      s_m[wave][row] = mx;
-      s_s[wave][row] = e;
+    zs[i] = BF16 ? (c[0][i] + c[1][i]) + (c[2][i] + c[3][i])
+                 : unsplit(c[0][i] + c[NC - 3][i], (c[1][i] + c[2][i]) + (c[NC - 2][i] + c[NC - 1][i]), zscale);
+  }
+  joiner_small_epilogue<TOPK>(m, a, ct, js, zs, bias);
+}
+
+// The small tile with fp32 products (direct models): the same tile, W read from the copy of
+// the per-stream kernels in chunks of 128 of K, the next chunk on its way during one's
+// MFMAs, K ending at C rounded up to 16.
+template <bool TOPK>
+__global__ __launch_bounds__(256) void k_joiner_direct(ModelDev m, JoinArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ JoinShared js;
+  int rt, ct;
+  if (!joiner_tile_of(blockIdx.x, a.n_ct, rt, ct)) return;
+  constexpr int BM = 16, KC = 128, U = 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lr = lane & 15, lg = lane >> 4;
+  const int r0 = rt * BM, K = m.direct, col = ct * kJoinerBN + 16 * wave + lr;
+  const float4* __restrict__ wi = reinterpret_cast<const float4*>(m.Wi);
+  const size_t Vp = (size_t)m.Vpad;
+  float4 w[KC / 16], wn[KC / 16];
+  auto load_w = [&](int kc, float4(&x)[KC / 16]) {  // (zeros from C up to Kpad, a multiple of KC)
+#pragma unroll
+    for (int s = 0; s < KC / 16; ++s) x[s] = wi[(size_t)(kc / 4 + lg + 4 * s) * Vp + col];
+  };
+  load_w(0, w);
+  const float bias = col < m.V ? m.bias[col] : 0.f;
+  const int act = tid < BM ? (int)joiner_row_active(a, r0 + tid) : 0;
+  if (tid < BM) js.row[tid] = act ? r0 + tid : -1;
+  if (!__syncthreads_or(act)) return;  // uniform: no row in this tile
+  // the tile's h rows (of rows past the batch, its last: their results are dropped)
+  float* s_h = reinterpret_cast<float*>(smem);
+  const int ldk = K + 4, cpr = K / 4, nchunk = BM * cpr;
+  const uint4* hsrc = reinterpret_cast<const uint4*>(a.h);
+  for (int c0 = tid; c0 < nchunk; c0 += 256 * U) {
+    uint4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int c = min(c0 + 256 * u, nchunk - 1), r = c / cpr;
+      v[u] = hsrc[(size_t)min(r0 + r, a.R - 1) * (m.Kpad / 4) + (c - r * cpr)];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int c = c0 + 256 * u, r = c / cpr;
+      if (c < nchunk)
+        *reinterpret_cast<uint4*>(s_h + (size_t)r * ldk + 4 * (c - r * cpr)) =
+            make_uint4(v[u].x, v[u].y, v[u].z, v[u].w);
     }
   }
   __syncthreads();
-  if (tid < BM && s_row[tid] >= 0) {
-    float M = s_m[0][tid];
-    for (int w = 1; w < 4; ++w) M = fmaxf(M, s_m[w][tid]);
-    float S = 0.f;
-    for (int w = 0; w < 4; ++w) S += s_s[w][tid] == 0.f ? 0.f : s_s[w][tid] * expf(s_m[w][tid] - M);
-    a.stats[(size_t)s_row[tid] * nvt + ct] = make_float2(M, S);
-  }
-  // logits (general graphs) or each row's best KT labels per 16-column sub-tile
-  // (trivial graph), found with DPP row reductions
-  const int nsub = nvt * (kJoinerBN / 16);
+  f32x4 acc[4];  // one chain per k modulo 4
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = s_row[4 * lg + i];
-    const float z = zr[i];
-    const bool act = row >= 0;
-    if (!TOPK) {
-      if (act && cvalid) a.logits[(size_t)row * (nvt * kJoinerBN) + col] = z;
-    } else {
-      unsigned long long key = (cvalid && col >= 1)
-                                   ? ((unsigned long long)f2ord(z) << 32) | (0xffffffffu - (unsigned)col)
-                                   : 0ull;
-      const size_t ob = ((size_t)max(row, 0) * nsub + ct * (kJoinerBN / 16) + wave) * a.KT;
-      for (int q = 0; q < a.KT; ++q) {
-        const unsigned long long best = row16_max_u64(key);
-        if (act && best != 0ull && key == best) {
-          a.tk_z[ob + q] = z;
-          a.tk_c[ob + q] = col;
-        }
-        if (act && best == 0ull && lr == 0) {
-          a.tk_z[ob + q] = -INFINITY;
-          a.tk_c[ob + q] = -1;
-        }
-        if (key == best) key = 0ull;
-      }
-      if (act && ct == 0 && wave == 0 && lr == 0) a.z0[row] = z;
+  for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const float* hr = s_h + (size_t)lr * ldk + 4 * lg;
+  for (int kc = 0; kc < K; kc += KC) {
+    if (kc + KC < K) load_w(kc + KC, wn);
+#pragma unroll
+    for (int s = 0; s < KC / 16; ++s) {
+      if (kc + 16 * s >= K) break;  // uniform
+      const float4 h = *reinterpret_cast<const float4*>(hr + kc + 16 * s);
+      acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(h.x, w[s].x, acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(h.y, w[s].y, acc[1], 0, 0, 0);
+      acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(h.z, w[s].z, acc[2], 0, 0, 0);
+      acc[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(h.w, w[s].w, acc[3], 0, 0, 0);
     }
+#pragma unroll
+    for (int s = 0; s < KC / 16; ++s) w[s] = wn[s];
   }
+  float zs[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) zs[i] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
+  joiner_small_epilogue<TOPK>(m, a, ct, js, zs, bias);
 }
 
 template <bool BF16, bool TOPK>
@@ -3846,6 +3951,20 @@ hipError_t launch_joiner_small(const ModelDev& m, const JoinArgs& a, const Joine
   return hipGetLastError();
 }
 
+template <bool TOPK>
+hipError_t launch_joiner_direct(const ModelDev& m, const JoinArgs& a, const JoinerPlan& p,
+                                hipStream_t st) {
+  static size_t attr = 0;
+  if (p.lds > 65536 && p.lds > attr) {
+    hipError_t e = hipFuncSetAttribute((const void*)k_joiner_direct<TOPK>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
+    if (e != hipSuccess) return e;
+    attr = p.lds;
+  }
+  launch_k((k_joiner_direct<TOPK>), dim3(p.grid), dim3(256), p.lds, st, m, a);
+  return hipGetLastError();
+}
+
 template <bool BF16, bool TOPK, bool DENSE>
 hipError_t launch_joiner_sweep(const ModelDev& m, const JoinArgs& a, const JoinerPlan& p,
                                hipStream_t st) {
@@ -3887,6 +4006,8 @@ hipError_t launch_joiner(const ModelDev& m, const JoinArgs& a, const JoinerPlan&
     return topk ? launch_joiner_t<false, true, 2, 2>(m, a, p, st)
                 : launch_joiner_t<false, false, 2, 2>(m, a, p, st);
   }
+  if (m.direct)
+    return topk ? launch_joiner_direct<true>(m, a, p, st) : launch_joiner_direct<false>(m, a, p, st);
   if (m.bf16)
     return topk ? launch_joiner_small<true, true>(m, a, p, st) : launch_joiner_small<true, false>(m, a, p, st);
   return topk ? launch_joiner_small<false, true>(m, a, p, st) : launch_joiner_small<false, false>(m, a, p, st);
@@ -3909,12 +4030,21 @@ bool take_launch_events(hipEvent_t* start, hipEvent_t* stop) {
   return true;
 }
 
-JoinerPlan plan_joiner(int rows, int Vpad, int Kpad, int bf16, int ncu, bool topk) {
+JoinerPlan plan_joiner(const ModelDev& m, int rows, int ncu, bool topk) {
+  const int Vpad = m.Vpad, Kpad = m.Kpad, bf16 = m.bf16;
   JoinerPlan p;
   p.shape = 0;
   p.small = p.sweep = false;
   const int esz = bf16 ? 2 : 4;
   const int nvt = Vpad / kJoinerBN;
+  if (m.direct) {
+    p.small = true;
+    p.n_rt = (rows + 15) / 16;
+    p.n_ct = nvt;
+    p.grid = joiner_grid(p.n_rt, p.n_ct);
+    p.lds = (size_t)16 * (m.direct + 4) * sizeof(float);
+    return p;
+  }
   // bf16 logits: 256 x 256 GEMM tiles when they give every compute unit several
   if (bf16 && !topk) {
     p.n_rt = (rows + kJWideBM - 1) / kJWideBM;
@@ -3968,10 +4098,10 @@ JoinerPlan plan_joiner(int rows, int Vpad, int Kpad, int bf16, int ncu, bool top
 hipError_t launch_model_setup(const float* embed, const float* conv, const float* w_out,
                               const float* b_out, int V, int C, int Kpad, int Vpad, int bf16,
                               float* P0, float* P1, uint16_t* Ws, uint16_t* Wsi, float* zscale,
-                              uint16_t* Wb, void* Wi, float* bias, hipStream_t st) {
+                              int* wide, uint16_t* Wb, void* Wi, float* bias, hipStream_t st) {
   hipLaunchKernelGGL(k_model_setup, dim3((Vpad + 3) / 4), dim3(256), 0, st,
-                     embed, conv, w_out, b_out, V, C, Kpad, Vpad, bf16, P0, P1, Ws, Wsi, zscale, Wb,
-                     Wi, bias);
+                     embed, conv, w_out, b_out, V, C, Kpad, Vpad, bf16, P0, P1, Ws, Wsi, zscale,
+                     wide, Wb, Wi, bias);
   return hipGetLastError();
 }
 
@@ -4216,7 +4346,7 @@ hipError_t launch_joiner_dense(const ModelDev& m, const float* enc, long long en
 hipError_t launch_joiner_gemm(const ModelDev& m, const void* h, int R, float* logits,
                               float2* stats, int ncu, hipStream_t st) {
   if (R <= 0) return hipSuccess;
-  const JoinerPlan p = plan_joiner(R, m.Vpad, m.Kpad, m.bf16, ncu);
+  const JoinerPlan p = plan_joiner(m, R, ncu);
   JoinArgs a{};
   a.h = h;
   a.logits = logits;

@@ -160,7 +160,7 @@ def test_joiner_weight_scales(scale, V, C, R):
     assert (np.abs(got - want) <= tol).all()
 
 
-@pytest.mark.parametrize("p", [0, 20, 24, 27])
+@pytest.mark.parametrize("p", [0, 20, 24, 27, 40, 100])
 @pytest.mark.parametrize("where", ["row", "column"])
 @pytest.mark.parametrize("V,C,R", RANGE_SHAPES)
 def test_joiner_weight_range(V, C, R, where, p):
@@ -174,7 +174,7 @@ def test_joiner_weight_range(V, C, R, where, p):
     own = np.abs(m.w_out).max()
     if where == "row":
         m.w_out[3] *= np.float32(2.0 ** p)
-        m.b_out[3] = -1e30
+        m.b_out[3] = -3e38
     else:
         m.w_out[:, 7] = np.float32(0.05 * 2.0 ** p)
         m.embed[:, 7] = 0
@@ -184,3 +184,25 @@ def test_joiner_weight_range(V, C, R, where, p):
     err = np.abs(got - want)[:, keep].max()
     say(f"  {where} 2^{p}: max |dlogp| = {err:.3g}")
     assert err <= 2e-7 * np.abs(want[:, keep]).max() + 2 * LOGIT_EPS * np.sqrt(C) * own
+
+
+@pytest.mark.parametrize("V,C,R", RANGE_SHAPES)
+def test_joiner_infinite_weight(V, C, R):
+    """A weight of minus infinity on a positive unit makes its label impossible and leaves
+    the others alone."""
+    rng = np.random.default_rng(V + C + 1)
+    m = synth.make_model(rng, V, C, 0.05)
+    enc = rng.standard_normal((R, C), dtype=np.float32)
+    a, b = rng.integers(0, V, R), rng.integers(0, V, R)
+    own = np.abs(m.w_out).max()
+    m.w_out[3, 7] = -np.inf
+    m.embed[:, 7] = 0
+    enc[:, 7] = rng.uniform(0.1, 2.0, R)
+    got = _logp_gpu(m, enc, a, b)
+    keep = np.arange(V) != 3
+    m.w_out[3, 7] = 0
+    m.b_out[3] = -3e38
+    want = _logp64(m, enc, a, b)
+    assert (got[:, 3] == -np.inf).all()
+    assert np.abs(got - want)[:, keep].max() <= (2e-7 * np.abs(want[:, keep]).max() +
+                                                 2 * LOGIT_EPS * np.sqrt(C) * own)
