@@ -621,42 +621,78 @@ __device__ __forceinline__ int active_contexts(const JoinArgs& a, int b) {
   return a.t < len ? n : 0;
 }
 
-// The rows of a tile: entries [r0, r0 + BM) of the batch's active rows, in (stream,
-// context slot) order, into s_row (-1 past the last); false if there are none.  Rows are
-// b * Nc + j for the j < nctx[b] contexts of a stream within its length: packing them
-// leaves no tile of the grid, which is sized for Nc rows per stream, with holes (a beam
-// keeps about half of the contexts it may).  Each thread takes consecutive streams.
-// Every thread calls it; it ends with a barrier.
-template <int NT, int BM>
-__device__ __forceinline__ bool joiner_tile_rows(const JoinArgs& a, int r0, int* s_row, int* s_wsum) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (a.rows_mode) {
-    for (int i = tid; i < BM; i += NT) s_row[i] = r0 + i < a.R ? r0 + i : -1;
-    __syncthreads();
-    return r0 < a.R;
-  }
-  const int per = (a.B + NT - 1) / NT, b0 = min(tid * per, a.B), b1 = min(b0 + per, a.B);
-  int n = 0;
-  for (int b = b0; b < b1; ++b) n += active_contexts(a, b);
-  for (int i = tid; i < BM; i += NT) s_row[i] = -1;
-  const int incl = (int)wave_incl_scan_u32((unsigned)n);
-  if (lane == 63) s_wsum[wave] = incl;
-  __syncthreads();
-  int pos = incl - n, total = 0;
+// The batch's active rows in (stream, context slot) order: rows b * Nc + j for the j <
+// nctx[b] contexts of each stream within its length.  Packing them leaves no tile of a
+// grid, which is sized for Nc rows per stream, with holes (a beam keeps about half of the
+// contexts it may).  Each thread takes consecutive streams; the counts of the first few
+// stay in registers (a second read would be one more round trip).
+template <int NT>
+struct PackedRows {
+  static constexpr int kHeld = 4;
+  int b0, b1, pos, total;  // this thread's streams, the rows before them, all rows
+  int held[kHeld];
+  // Every thread calls it; s_wsum: [NT / 64].  One barrier (of LDS accesses only: loads
+  // requested before it stay in flight).
+  __device__ __forceinline__ void count(const JoinArgs& a, int* s_wsum) {
+    const int tid = threadIdx.x, wave = tid >> 6;
+    const int per = (a.B + NT - 1) / NT;
+    b0 = min(tid * per, a.B);
+    b1 = min(b0 + per, a.B);
+    int n = 0;
 #pragma unroll
-  for (int w = 0; w < NT / 64; ++w) {
-    const int x = s_wsum[w];
-    if (w < wave) pos += x;
-    total += x;
-  }
-  if (pos < r0 + BM && pos + n > r0)
-    for (int b = b0; b < b1; ++b) {
-      const int nb = active_contexts(a, b);
-      for (int j = max(0, r0 - pos); j < nb && pos + j < r0 + BM; ++j) s_row[pos + j - r0] = b * a.Nc + j;
-      pos += nb;
+    for (int i = 0; i < kHeld; ++i) {
+      held[i] = 0;
+      if (b0 + i < b1) held[i] = active_contexts(a, b0 + i);
+      n += held[i];
     }
-  __syncthreads();
-  return r0 < total;
+    for (int b = b0 + kHeld; b < b1; ++b) n += active_contexts(a, b);
+    const int incl = (int)wave_incl_scan_u32((unsigned)n);
+    if ((tid & 63) == 63) s_wsum[wave] = incl;
+    lds_only_barrier();
+    pos = incl - n;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) {
+      const int x = s_wsum[w];
+      if (w < wave) pos += x;
+      total += x;
+    }
+  }
+  // list[i - r0] = active row i for i in [r0, r1)
+  __device__ __forceinline__ void write(const JoinArgs& a, int r0, int r1, int* list) const {
+    if (pos >= r1) return;
+    int p = pos;
+    auto put = [&](int b, int nb) {
+      for (int j = max(0, r0 - p); j < nb && p + j < r1; ++j) list[p + j - r0] = b * a.Nc + j;
+      p += nb;
+    };
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i) put(b0 + i, held[i]);
+    for (int b = b0 + kHeld; b < b1 && p < r1; ++b) put(b, active_contexts(a, b));
+  }
+};
+
+// The rows of a tile: entries [r0, r0 + BM) of the batch's active rows into s_row (-1 past
+// the last).  0: there are none; 2: they are rows r0 and on themselves (every row of the
+// batch is active), and s_row is to be read after the caller's next barrier only; else 1.
+// Every thread calls it.
+template <int NT, int BM>
+__device__ __forceinline__ int joiner_tile_rows(const JoinArgs& a, int r0, int* s_row, int* s_wsum) {
+  const int tid = threadIdx.x;
+  PackedRows<NT> rows;
+  rows.total = a.R;
+  if (!a.rows_mode) {
+    for (int i = tid; i < BM; i += NT) s_row[i] = -1;
+    rows.count(a, s_wsum);
+  }
+  if (r0 >= rows.total) return 0;
+  if (rows.total == a.R) {
+    for (int i = tid; i < BM; i += NT) s_row[i] = r0 + i < a.R ? r0 + i : -1;
+    return 2;
+  }
+  rows.write(a, r0, r0 + BM, s_row);
+  lds_only_barrier();
+  return 1;
 }
 
 // Tile of workgroup i, which runs on XCD i mod 8.  When the column tiles divide (nearly)
@@ -1043,23 +1079,13 @@ __global__ __launch_bounds__(128 * WN, MBW == 2 ? 3 : 1) void k_joiner(ModelDev 
   const int r0 = rt * BM, c0 = ct * BN;
   const int Kpad = m.Kpad, V = m.V, Vpad = m.Vpad, nvt = a.nvt;
   const int vt = WN * ct + wc;  // this wave's vocabulary tile
-  if (!joiner_tile_rows<NT, BM>(a, r0, s_row, s_wsum)) return;  // uniform: no row in this tile
-  // the epilogue's bias and scale values, requested now so that their round trip is hidden
-  // behind the main loop (clamped: past the vocabulary they are never used)
-  float bias_r[4], zscale[4];
-#pragma unroll
-  for (int nb = 0; nb < 4; ++nb) {
-    const int col = min(64 * vt + 16 * nb + lr, V - 1);
-    bias_r[nb] = m.bias[col];
-    zscale[nb] = BF16 ? 1.f : m.zscale[col];
-  }
 
   // slice loads: UA (h) and UB (W) chunks of 16 bytes per thread (BM and BN rows x 8 chunks)
   const char* hsrc = reinterpret_cast<const char*>(a.h);
   const char* wsrc = reinterpret_cast<const char*>(BF16 ? m.Wb : m.Ws);
   const size_t rowb = (size_t)Kpad * ESZ;
   const unsigned rowb32 = (unsigned)rowb;  // h and W each stay below 4 GiB (checked at launch)
-  // byte offsets of this thread's h and W chunks in slice 0 (32 bits, from the uniform
+  // byte offsets of this thread's W and h chunks in slice 0 (32 bits, from the uniform
   // bases).  Rows past the tile's last or the padded vocabulary read a valid row: their
   // products land only in rows and columns the epilogue never writes.  (No branches
   // around the loads, so their waits stay exact.)
@@ -1068,26 +1094,53 @@ __global__ __launch_bounds__(128 * WN, MBW == 2 ? 3 : 1) void k_joiner(ModelDev 
   for (int u = 0; u < UB; ++u) {
     const int c = tid + NT * u, row = c >> 3, part = c & 7;
     wa[u] = (unsigned)min(c0 + row, Vpad - 1) * rowb32 + part * 16;
-    if (u < UA) ha[u < UA ? u : 0] = (unsigned)max(s_row[row], s_row[0]) * rowb32 + part * 16;
   }
   // slices in flight: register sets 0 and 1 (set 1 only with DEEP)
   uint4 ra0[UA], rb0[UB], ra1[UA], rb1[UB];
-  auto gload = [&](int s, int set) {
+  auto gload_w = [&](int s, int set) {
 #pragma unroll
     for (int u = 0; u < UB; ++u) {
-      const unsigned off = (unsigned)(s * kJSlice);
-      const uint4 vb = *reinterpret_cast<const uint4*>(wsrc + (wa[u] + off));
+      const uint4 vb = *reinterpret_cast<const uint4*>(wsrc + (wa[u] + (unsigned)(s * kJSlice)));
       if (set == 0)
         rb0[u] = vb;
       else
         rb1[u] = vb;
-      if (u < UA) {
-        const uint4 va = *reinterpret_cast<const uint4*>(hsrc + (ha[u < UA ? u : 0] + off));
-        if (set == 0)
-          ra0[u < UA ? u : 0] = va;
-        else
-          ra1[u < UA ? u : 0] = va;
-      }
+    }
+  };
+  auto gload_h = [&](int s, int set) {
+#pragma unroll
+    for (int u = 0; u < UA; ++u) {
+      const uint4 va = *reinterpret_cast<const uint4*>(hsrc + (ha[u] + (unsigned)(s * kJSlice)));
+      if (set == 0)
+        ra0[u] = va;
+      else
+        ra1[u] = va;
+    }
+  };
+  auto gload = [&](int s, int set) {
+    gload_w(s, set);
+    gload_h(s, set);
+  };
+  // W's first slices do not depend on the tile's rows
+  gload_w(0, 0);
+  if (DEEP) gload_w(1, 1);
+  const int rows = joiner_tile_rows<NT, BM>(a, r0, s_row, s_wsum);
+  if (rows == 0) return;  // uniform: no row in this tile
+#pragma unroll
+  for (int u = 0; u < UA; ++u) {
+    const int c = tid + NT * u;
+    const int r = rows == 2 ? min(r0 + (c >> 3), a.R - 1) : max(s_row[c >> 3], s_row[0]);
+    ha[u] = (unsigned)r * rowb32 + (c & 7) * 16;
+  }
+  // the epilogue's bias and scale values (clamped: past the vocabulary they are never used),
+  // requested before the last slice's MFMAs, where the slice registers are free
+  float bias_r[4], zscale[4];
+  auto load_columns = [&]() {
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) {
+      const int col = min(64 * vt + 16 * nb + lr, V - 1);
+      bias_r[nb] = m.bias[col];
+      zscale[nb] = BF16 ? 1.f : m.zscale[col];
     }
   };
   auto lstore = [&](int buf, int set) {
@@ -1181,8 +1234,8 @@ __global__ __launch_bounds__(128 * WN, MBW == 2 ? 3 : 1) void k_joiner(ModelDev 
     // slices of MFMAs to land; slice s + 1 goes to the other LDS buffer after them.
     // (The scheduling barriers keep each fetch ahead of the MFMAs and LDS writes that
     // follow it, where the compiler would otherwise sink it.)
-    gload(0, 0);
-    gload(1, 1);
+    gload_h(0, 0);
+    gload_h(1, 1);
     __builtin_amdgcn_sched_barrier(0);
     lstore(0, 0);
     __syncthreads();
@@ -1201,23 +1254,33 @@ __global__ __launch_bounds__(128 * WN, MBW == 2 ? 3 : 1) void k_joiner(ModelDev 
     compute(0);  // the last two slices
     lstore(1, 1);
     __syncthreads();
+    load_columns();
+    __builtin_amdgcn_sched_barrier(0);
     compute(1);
-  } else {
-    gload(0, 0);
+  } else {  // (an even number of slices: Kpad is a multiple of 512)
+    gload_h(0, 0);
     lstore(0, 0);
     __syncthreads();
-    for (int s = 0; s < nsl; s += 2) {
-      if (s + 1 < nsl) gload(s + 1, 0);
+    for (int s = 0; s + 2 < nsl; s += 2) {
+      gload(s + 1, 0);
       __builtin_amdgcn_sched_barrier(0);
       compute(0);
-      if (s + 1 < nsl) lstore(1, 0);
+      lstore(1, 0);
       __syncthreads();
-      if (s + 2 < nsl) gload(s + 2, 0);
+      gload(s + 2, 0);
       __builtin_amdgcn_sched_barrier(0);
       compute(1);
-      if (s + 2 < nsl) lstore(0, 0);
+      lstore(0, 0);
       __syncthreads();
     }
+    gload(nsl - 1, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    compute(0);
+    lstore(1, 0);
+    __syncthreads();
+    load_columns();
+    __builtin_amdgcn_sched_barrier(0);
+    compute(1);
   }
 
   // epilogue of this wave's vocabulary tile (none beyond the padded vocabulary)
@@ -1361,35 +1424,18 @@ __global__ __launch_bounds__(kSweepThreads) void k_joiner_sweep(ModelDev m, Join
   }
 
   // this group's rows: blocks [grp * q, (grp + 1) * q) of the active rows, q blocks each
-  int total = a.R, per = 0, b0 = 0, b1 = 0, pos = 0;
-  if (!DENSE) {  // pack the active rows in (stream, context slot) order
-    per = (a.B + NT - 1) / NT;
-    b0 = min(tid * per, a.B);
-    b1 = min(b0 + per, a.B);
-    int n = 0;
-    for (int b = b0; b < b1; ++b) n += active_contexts(a, b);
-    const int incl = (int)wave_incl_scan_u32((unsigned)n);
-    if (lane == 63) s_wsum[wave] = incl;
-    __syncthreads();
-    pos = incl - n;
-    total = 0;
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w) {
-      const int x = s_wsum[w];
-      if (w < wave) pos += x;
-      total += x;
-    }
+  int total = a.R;
+  PackedRows<NT> rows;
+  if (!DENSE) {
+    rows.count(a, s_wsum);
+    total = rows.total;
   }
   const int blocks = (total + 15) / 16, q = (blocks + a.n_rt - 1) / a.n_rt;
   const int r0 = grp * q * 16, nrow = min(q * 16, total - r0);
   if (nrow <= 0) return;  // uniform
   const int nblk = (nrow + 15) / 16;
   if (!DENSE) {
-    for (int b = b0; b < b1; ++b) {
-      const int nb = active_contexts(a, b);
-      for (int j = max(0, r0 - pos); j < nb && pos + j < r0 + nrow; ++j) list[pos + j - r0] = b * a.Nc + j;
-      pos += nb;
-    }
+    rows.write(a, r0, r0 + nrow, list);
     __syncthreads();
   }
   // row i of the group (past its last: the last, whose results are dropped)
