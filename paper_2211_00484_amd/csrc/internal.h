@@ -155,7 +155,8 @@ struct DecodeDev {
 };
 
 struct JoinerPlan {
-  bool small;               // 16 x 64 tiles (direct models: always)
+  bool small;               // 16 MB x 64 tiles (direct models: always, MB = 1)
+  int MB;
   bool sweep;               // sweep (n_ct column tiles x n_rt row groups); else GEMM tiles (shape)
   int shape;                // GEMM tiles: 0 = 64 x 128, 1 = 256 x 256 (bf16)
   int n_rt, n_ct;           // row and column tiles

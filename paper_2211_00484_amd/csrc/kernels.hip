@@ -699,17 +699,18 @@ __device__ __forceinline__ int joiner_tile_rows(const JoinArgs& a, int r0, int* 
 // evenly by 8, XCD x owns the column tiles x, x + 8, ... and walks row tiles in order, its
 // column tiles fastest: its W columns stay in its L2 while each h row tile is read once per
 // XCD.  Otherwise some XCDs would hold more of them (all the work, for few column tiles),
-// and the tiles go round in row-major order.
-__host__ __device__ inline int joiner_xcd_cols(int n_ct) {  // column tiles per XCD, or 0
+// and the tiles go round in row-major order, unless an XCD's 32 compute units take its share
+// at once anyway.
+__host__ __device__ inline int joiner_xcd_cols(int n_rt, int n_ct) {  // column tiles per XCD, or 0
   const int n = (n_ct + 7) / 8;
-  return 8 * (8 * n - n_ct) <= n_ct ? n : 0;
+  return 8 * (8 * n - n_ct) <= n_ct || n_rt * n <= 32 ? n : 0;
 }
 inline int joiner_grid(int n_rt, int n_ct) {
-  const int n = joiner_xcd_cols(n_ct);
+  const int n = joiner_xcd_cols(n_rt, n_ct);
   return (n ? 8 * n : n_ct) * n_rt;
 }
-__device__ __forceinline__ bool joiner_tile_of(int i, int n_ct, int& rt, int& ct) {
-  const int n = joiner_xcd_cols(n_ct);
+__device__ __forceinline__ bool joiner_tile_of(const JoinArgs& a, int i, int& rt, int& ct) {
+  const int n_ct = a.n_ct, n = joiner_xcd_cols(a.n_rt, n_ct);
   if (n) {
     const int slot = i >> 3;
     rt = slot / n;
@@ -736,24 +737,28 @@ __device__ __forceinline__ void stage_chunk(unsigned char* row, int cc, const ui
   }
 }
 
-// Small joiner tile, for batches with few tiles per compute unit: 16 rows x 64 vocabulary
+// Small joiner tile, for batches with few tiles per compute unit: 16 MB rows x 64 vocabulary
 // columns; wave w owns columns 16w..16w+15 and keeps its W fragment (16 columns x up to
-// 512 of K) in registers; the tile's h rows are staged once in LDS.  (Tiles of 32 and 64
-// rows, which reuse W, measured slower at every size: fewer workgroups in flight.)
+// 512 of K) in registers; the tile's h rows are staged once in LDS.  MB = 2 (bf16, C in
+// 513 .. 1,024, a tile per compute unit) uses each W fragment twice: V = 1,000, C = 640,
+// 1,024 rows 12.2 us against 14.8.  (With C <= 512 the sweep has those batches; 64 rows, or
+// 32 with fp16 pairs, do not leave the LDS of a compute unit to two workgroups.)
+constexpr int kSmallMB = 2;  // at most
 struct JoinShared {
-  int row[16];
-  float m[4][16], s[4][16];
+  int row[16 * kSmallMB];
+  float m[4][16 * kSmallMB], s[4][16 * kSmallMB];
 };
 
-// Epilogue of a small tile: zs are the lane's products for rows 4 lg + i of the tile, without
-// the bias of its column.
-template <bool TOPK>
+// Epilogue of a small tile: zs[mb] are the lane's products for rows 16 mb + 4 lg + i of the
+// tile, without the bias of its column.
+template <bool TOPK, int MB>
 __device__ __forceinline__ void joiner_small_epilogue(const ModelDev& m, const JoinArgs& a, int ct,
-                                                      JoinShared& js, const float (&zs)[4], float bias) {
+                                                      JoinShared& js, const float (&zs)[MB][4],
+                                                      float bias) {
   const int* s_row = js.row;
-  float(*s_m)[16] = js.m;
-  float(*s_s)[16] = js.s;
-  constexpr int BM = 16;
+  float(*s_m)[16 * kSmallMB] = js.m;
+  float(*s_s)[16 * kSmallMB] = js.s;
+  constexpr int BM = 16 * MB;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 15, lg = lane >> 4, nvt = a.n_ct;
   const int col = ct * kJoinerBN + 16 * wave + lr;
@@ -761,12 +766,13 @@ __device__ __forceinline__ void joiner_small_epilogue(const ModelDev& m, const J
   // epilogue.  First everything that needs the workgroup barrier (per-row max
   // and sum exp over the tile, combined across the 4 waves in LDS); the global
   // stores come after it, so the barrier never waits on them.
-  float zr[4];
+  float zr[MB][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = 4 * lg + i;  // the 16 lanes of a DPP row share this row
-    const float z = cvalid ? zs[i] + bias : -INFINITY;
-    zr[i] = z;
+  for (int mi = 0; mi < 4 * MB; ++mi) {
+    const int mb = mi / 4, i = mi % 4;
+    const int row = 16 * mb + 4 * lg + i;  // the 16 lanes of a DPP row share this row
+    const float z = cvalid ? zs[mb][i] + bias : -INFINITY;
+    zr[mb][i] = z;
     const float mx = row16_max(z);
     const float e = row16_sum(cvalid ? expf(z - mx) : 0.f);
     if (lr == 0) {
@@ -786,9 +792,9 @@ __device__ __forceinline__ void joiner_small_epilogue(const ModelDev& m, const J
   // (trivial graph), found with DPP row reductions
   const int nsub = nvt * (kJoinerBN / 16);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = s_row[4 * lg + i];
-    const float z = zr[i];
+  for (int mi = 0; mi < 4 * MB; ++mi) {
+    const int row = s_row[16 * (mi / 4) + 4 * lg + mi % 4];
+    const float z = zr[mi / 4][mi % 4];
     const bool act = row >= 0;
     if (!TOPK) {
       if (act && cvalid) a.logits[(size_t)row * (nvt * kJoinerBN) + col] = z;
@@ -815,12 +821,13 @@ __device__ __forceinline__ void joiner_small_epilogue(const ModelDev& m, const J
 }
 
 // One joiner tile of frame a.t.  Uniform
-// across the workgroup; a tile without active rows computes nothing.
-template <bool BF16, bool TOPK>
+// across the workgroup; a tile without active rows computes nothing.  U: 16-byte chunks of
+// h per thread and batch of loads.
+template <bool BF16, bool TOPK, int MB, int U>
 __device__ __forceinline__ void joiner_tile_small(const ModelDev& m, const JoinArgs& a, int ct, int rt,
                                             unsigned char* smem, JoinShared& js) {
   int* s_row = js.row;
-  constexpr int BM = 16;
+  constexpr int BM = 16 * MB;
   constexpr int ESZ = BF16 ? 2 : 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r0 = rt * BM, n0 = ct * kJoinerBN;
@@ -829,23 +836,28 @@ __device__ __forceinline__ void joiner_tile_small(const ModelDev& m, const JoinA
   const int col = n0 + 16 * wave + lr;
   const bool cvalid = col < V;
 
-  // The tile's h rows, for LDS: the first of a wave's loads, requested before anything is
-  // known of the rows (rows past the batch read its last; a row's products reach only its
-  // own results, which are dropped unless it is active).
-  constexpr int U = BF16 ? 4 : 8;                    // 16-byte chunks per thread and batch
+  // The tile's h rows, for LDS: with one row block the first of a wave's loads, requested
+  // before anything is known of the rows (rows past the batch read its last chunk; a row's
+  // products reach only its own results, which are dropped unless it is active).
   const int ldk = Kpad + (BF16 ? 8 : 4);             // row stride in elements (16-byte pad)
   const int cpr = Kpad * ESZ / 16;                   // 16-byte chunks per row
   const int nchunk = BM * cpr;
-  const uint4* hsrc = reinterpret_cast<const uint4*>(a.h);
+  const uint4* hsrc = reinterpret_cast<const uint4*>(a.h) + (size_t)r0 * cpr;
+  const int last = min(nchunk, (a.R - r0) * cpr) - 1;
   uint4 hv[U];
   auto load_h = [&](int c0) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int c = min(c0 + tid + u * 256, nchunk - 1), r = c / cpr;
-      hv[u] = hsrc[(size_t)min(r0 + r, a.R - 1) * cpr + (c - r * cpr)];
+      if (MB == 1) {
+        hv[u] = hsrc[(unsigned)min(c0 + tid + u * 256, last)];
+      } else {  // (batches bound by their loads rather than latency: active rows only)
+        const int c = c0 + tid + u * 256;
+        hv[u] = make_uint4(0, 0, 0, 0);
+        if (c < nchunk && s_row[c / cpr] >= 0) hv[u] = hsrc[(unsigned)c];
+      }
     }
   };
-  load_h(0);
+  if (MB == 1) load_h(0);
   // W fragment of the first K chunk (registers) and the bias: issued before the
   // h staging so that all of the tile's loads are in flight together
   // (Kpad is a multiple of 512: one chunk of W per lane is 16 uint4 of bf16, or of high
@@ -881,7 +893,7 @@ __device__ __forceinline__ void joiner_tile_small(const ModelDev& m, const JoinA
   if (!__syncthreads_or(act)) return;  // uniform: no row in this tile
 
   for (int c0 = 0; c0 < nchunk; c0 += 256 * U) {
-    if (c0 > 0) load_h(c0);
+    if (MB > 1 || c0 > 0) load_h(c0);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int c = c0 + tid + u * 256;
@@ -896,9 +908,11 @@ __device__ __forceinline__ void joiner_tile_small(const ModelDev& m, const JoinA
   // block, chain), so no MFMA waits for the one before it: four for bf16; for fp16 pairs
   // the sums of high x high, high x low and low x high, over even and odd k-steps each.
   constexpr int NC = BF16 ? 4 : 6;
-  f32x4 acc[NC];
+  f32x4 acc[MB][NC];
 #pragma unroll
-  for (int c = 0; c < NC; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[mb][c] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   for (int kc = 0; kc < Kpad; kc += 512) {
     if (kc > 0) load_w(kc);  // later K chunks (C > 512)
@@ -906,12 +920,14 @@ __device__ __forceinline__ void joiner_tile_small(const ModelDev& m, const JoinA
     if (BF16) {
       const uint16_t* hb = reinterpret_cast<const uint16_t*>(smem) + (size_t)lr * ldk + kc + 16 * lg;
 #pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        const uint16_t* hr = hb + s * 64;
+      for (int s = 0; s < 8; ++s)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        const uint16_t* hr = hb + (size_t)mb * 16 * ldk + s * 64;
         const uint4 a0 = *reinterpret_cast<const uint4*>(hr);
         const uint4 a1 = *reinterpret_cast<const uint4*>(hr + 8);
-        f32x4& c0 = acc[(2 * s) & 3];
-        f32x4& c1 = acc[(2 * s + 1) & 3];
+        f32x4& c0 = acc[mb][(2 * s) & 3];
+        f32x4& c1 = acc[mb][(2 * s + 1) & 3];
         c0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a0), as_bf16x8(wb[2 * s]), c0, 0, 0, 0);
         c1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a1), as_bf16x8(wb[2 * s + 1]), c1, 0, 0, 0);
       }
@@ -923,7 +939,7 @@ __device__ __forceinline__ void joiner_tile_small(const ModelDev& m, const JoinA
         const f16x8 ah = as_f16x8(*reinterpret_cast<const uint4*>(hr));
         const f16x8 al = as_f16x8(*reinterpret_cast<const uint4*>(hr + 8));
         const f16x8 bh = as_f16x8(wb[s]), bl = as_f16x8(wl[BF16 ? 0 : s]);
-        f32x4* c = acc + (NC == 6 ? 3 * (s & 1) : 0);
+        f32x4* c = acc[0] + (NC == 6 ? 3 * (s & 1) : 0);
         c[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh, c[0], 0, 0, 0);
         c[2] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, bh, c[2], 0, 0, 0);
         c[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bl, c[1], 0, 0, 0);
@@ -931,14 +947,16 @@ __device__ __forceinline__ void joiner_tile_small(const ModelDev& m, const JoinA
     }
   }
 
-  float zs[4];
+  static_assert(BF16 || MB == 1, "fp16 pairs: one row block");
+  float zs[MB][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const f32x4* c = acc;
-    zs[i] = BF16 ? (c[0][i] + c[1][i]) + (c[2][i] + c[3][i])
+  for (int mi = 0; mi < 4 * MB; ++mi) {
+    const f32x4* c = acc[mi / 4];
+    const int i = mi % 4;
+    zs[mi / 4][i] = BF16 ? (c[0][i] + c[1][i]) + (c[2][i] + c[3][i])
                  : unsplit(c[0][i] + c[NC - 3][i], (c[1][i] + c[2][i]) + (c[NC - 2][i] + c[NC - 1][i]), zscale);
   }
-  joiner_small_epilogue<TOPK>(m, a, ct, js, zs, bias);
+  joiner_small_epilogue<TOPK, MB>(m, a, ct, js, zs, bias);
 }
 
 // The small tile with fp32 products (direct models): the same tile, W read from the copy of
@@ -949,7 +967,7 @@ __global__ __launch_bounds__(256) void k_joiner_direct(ModelDev m, JoinArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ JoinShared js;
   int rt, ct;
-  if (!joiner_tile_of(blockIdx.x, a.n_ct, rt, ct)) return;
+  if (!joiner_tile_of(a, blockIdx.x, rt, ct)) return;
   constexpr int BM = 16, KC = 128, U = 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 15, lg = lane >> 4;
@@ -1004,19 +1022,19 @@ __global__ __launch_bounds__(256) void k_joiner_direct(ModelDev m, JoinArgs a) {
 #pragma unroll
     for (int s = 0; s < KC / 16; ++s) w[s] = wn[s];
   }
-  float zs[4];
+  float zs[1][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) zs[i] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
-  joiner_small_epilogue<TOPK>(m, a, ct, js, zs, bias);
+  for (int i = 0; i < 4; ++i) zs[0][i] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
+  joiner_small_epilogue<TOPK, 1>(m, a, ct, js, zs, bias);
 }
 
-template <bool BF16, bool TOPK>
+template <bool BF16, bool TOPK, int MB, int U>
 __global__ __launch_bounds__(256) void k_joiner_small(ModelDev m, JoinArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ JoinShared js;
   int rt, ct;
-  if (!joiner_tile_of(blockIdx.x, a.n_ct, rt, ct)) return;
-  joiner_tile_small<BF16, TOPK>(m, a, ct, rt, smem, js);
+  if (!joiner_tile_of(a, blockIdx.x, rt, ct)) return;
+  joiner_tile_small<BF16, TOPK, MB, U>(m, a, ct, rt, smem, js);
 }
 
 constexpr float kLog2e = 1.44269504088896341f;
@@ -1062,7 +1080,7 @@ __global__ __launch_bounds__(128 * WN, MBW == 2 ? 3 : 1) void k_joiner(ModelDev 
   const int bid = blockIdx.x, xcd = bid & 7, slot = bid >> 3;
   int rt, ct;
   if (WN == 2) {
-    if (!joiner_tile_of(bid, a.n_ct, rt, ct)) return;
+    if (!joiner_tile_of(a, bid, rt, ct)) return;
   } else {
     // Tiles in row-major order, tile q on XCD q mod 8: with a column-tile count that
     // is not a multiple of 8, each XCD still gets an equal share, and sees only the
@@ -3983,18 +4001,33 @@ hipError_t launch_joiner_t(const ModelDev& m, const JoinArgs& a, const JoinerPla
   return hipGetLastError();
 }
 
-template <bool BF16, bool TOPK>
-hipError_t launch_joiner_small(const ModelDev& m, const JoinArgs& a, const JoinerPlan& p,
-                               hipStream_t st) {
+template <bool BF16, bool TOPK, int MB, int U>
+hipError_t launch_joiner_small_t(const ModelDev& m, const JoinArgs& a, const JoinerPlan& p,
+                                 hipStream_t st) {
   static size_t attr = 0;
   if (p.lds > 65536 && p.lds > attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_joiner_small<BF16, TOPK>,
+    hipError_t e = hipFuncSetAttribute((const void*)k_joiner_small<BF16, TOPK, MB, U>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
     if (e != hipSuccess) return e;
     attr = p.lds;
   }
-  launch_k((k_joiner_small<BF16, TOPK>), dim3(p.grid), dim3(256), p.lds, st, m, a);
+  launch_k((k_joiner_small<BF16, TOPK, MB, U>), dim3(p.grid), dim3(256), p.lds, st, m, a);
   return hipGetLastError();
+}
+
+// bf16: the tile's h rows in one batch of loads up to K = 2,048; fp16 pairs, whose W takes
+// twice the registers, in batches of a K of 512.
+template <bool BF16, bool TOPK>
+hipError_t launch_joiner_small(const ModelDev& m, const JoinArgs& a, const JoinerPlan& p,
+                               hipStream_t st) {
+  if constexpr (BF16) {
+    if (p.MB == 2) return launch_joiner_small_t<true, TOPK, 2, 16>(m, a, p, st);
+    if (m.Kpad == 512) return launch_joiner_small_t<true, TOPK, 1, 4>(m, a, p, st);
+    if (m.Kpad == 1024) return launch_joiner_small_t<true, TOPK, 1, 8>(m, a, p, st);
+    return launch_joiner_small_t<true, TOPK, 1, 16>(m, a, p, st);
+  } else {
+    return launch_joiner_small_t<false, TOPK, 1, 8>(m, a, p, st);
+  }
 }
 
 template <bool TOPK>
@@ -4080,6 +4113,7 @@ JoinerPlan plan_joiner(const ModelDev& m, int rows, int ncu, bool topk) {
   const int Vpad = m.Vpad, Kpad = m.Kpad, bf16 = m.bf16;
   JoinerPlan p;
   p.shape = 0;
+  p.MB = 1;
   p.small = p.sweep = false;
   const int esz = bf16 ? 2 : 4;
   const int nvt = Vpad / kJoinerBN;
@@ -4136,8 +4170,12 @@ JoinerPlan plan_joiner(const ModelDev& m, int rows, int ncu, bool topk) {
     }
   }
   p.small = true;
+  if (bf16 && Kpad == 1024 && (long long)((rows + 31) / 32) * nvt >= ncu) {
+    p.MB = 2;
+    p.n_rt = (rows + 31) / 32;
+  }
   p.grid = joiner_grid(p.n_rt, p.n_ct);
-  p.lds = (size_t)16 * (Kpad + (bf16 ? 8 : 4)) * esz;
+  p.lds = (size_t)16 * p.MB * (Kpad + (bf16 ? 8 : 4)) * esz;
   return p;
 }
 
