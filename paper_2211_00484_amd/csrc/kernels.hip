@@ -543,14 +543,16 @@ __device__ void write_h_rows_pairs(const ModelDev& m, const float* __restrict__ 
 
 // Rows of a dense (encoder row, context) table: batch row r is table row row0 + r,
 // with context ctx[row0 + r] (-1: an empty slot, written as zeros) and encoder row
-// enc + ((row0 + r) / per_enc) * enc_stride.  One wave per row, a column quad per lane and
-// step, the steps' loads in flight together (bound: the writes of h).  (32,000 rows, C = 512:
-// 46 us with a workgroup and a barrier per row.)
+// enc + ((row0 + r) / per_enc) * enc_stride.  One wave per 512 columns of a row, a column
+// quad per lane and step, both steps' loads in flight together (bound: the writes of h; few
+// rows: one round trip).  (32,000 rows, C = 512: 46 us with a workgroup and a barrier per
+// row.)
 __global__ __launch_bounds__(256) void k_h_rows(ModelDev m, const float* __restrict__ enc,
                                                 const int* __restrict__ ctx, long long row0,
                                                 int per_enc, long long enc_stride, int R,
                                                 void* __restrict__ h) {
-  const int lane = threadIdx.x & 63, r = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, wave = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int wpr = m.Kpad / 512, r = wave / wpr, k0 = 512 * (wave - r * wpr);
   if (r >= R) return;  // whole wave
   const long long g = row0 + r;
   const int c = ctx[g], C = m.C, Kpad = m.Kpad;
@@ -560,8 +562,8 @@ __global__ __launch_bounds__(256) void k_h_rows(ModelDev m, const float* __restr
   const int a = max(c, 0) / m.V, b = max(c, 0) - a * m.V;
   const float* P0 = m.P0 + (size_t)a * Kpad;
   const float* P1 = m.P1 + (size_t)b * Kpad;
-#pragma unroll 2
-  for (int k = 4 * lane; k < Kpad; k += 256) {
+#pragma unroll
+  for (int k = k0 + 4 * lane; k < k0 + 512; k += 256) {
     const float4 p0 = *reinterpret_cast<const float4*>(P0 + k);
     const float4 p1 = *reinterpret_cast<const float4*>(P1 + k);
     float4 x;
@@ -4413,7 +4415,7 @@ hipError_t launch_h_rows_dense(const ModelDev& m, const float* enc, long long en
                                const int* ctx, long long row0, int per_enc, int R, void* h,
                                hipStream_t st) {
   if (R <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_h_rows, dim3((R + 3) / 4), dim3(256), 0, st, m, enc, ctx, row0, per_enc,
+  hipLaunchKernelGGL(k_h_rows, dim3((R * (m.Kpad / 512) + 3) / 4), dim3(256), 0, st, m, enc, ctx, row0, per_enc,
                      enc_stride, R, h);
   return hipGetLastError();
 }
