@@ -491,9 +491,9 @@ namespace {
 template <int NT, bool CACHED>
 hipError_t launch_hyp_step_t(const ModelDev& m, const HypDev& d, int t, size_t lds,
                              const float* logits, const float2* stats, int* trace, hipStream_t st) {
+  static LdsGrant grant;
   if (lds > 32768) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_hyp_step<NT, CACHED>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const hipError_t e = grant((const void*)k_hyp_step<NT, CACHED>, lds);
     if (e != hipSuccess) return e;
   }
   hipEvent_t ea, eb;

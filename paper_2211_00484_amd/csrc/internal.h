@@ -3,7 +3,9 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <atomic>
 #include <cstdint>
+#include <mutex>
 
 namespace tbs {
 
@@ -27,6 +29,30 @@ constexpr size_t kMaxLds = 160 * 1024;  // LDS per workgroup on gfx950
 constexpr int kStreamMaxV = 512;     // per-stream kernel: vocabulary limit (8 logits per lane)
 constexpr int kMaxHyps = 16;         // full-sequence beam search: hypotheses per stream
 constexpr int kTransducerMaxK = 16;  // transducer recursions: cells per lane (U + 1 <= 1024)
+
+// Grants a kernel dynamic LDS beyond the default on the current device, once per device and
+// size (a launch per frame would otherwise pay for it each time).  One per kernel.
+class LdsGrant {
+ public:
+  hipError_t operator()(const void* kernel, size_t lds) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= kDevices)
+      return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (granted_[dev].load(std::memory_order_acquire) >= lds) return hipSuccess;
+    std::lock_guard<std::mutex> lk(mu_);  // (a smaller grant must not follow a larger one)
+    if (granted_[dev].load(std::memory_order_relaxed) >= lds) return hipSuccess;
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e == hipSuccess) granted_[dev].store(lds, std::memory_order_release);
+    return e;
+  }
+
+ private:
+  static constexpr int kDevices = 64;
+  std::atomic<size_t> granted_[kDevices] = {};
+  std::mutex mu_;
+};
 
 inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
@@ -163,6 +189,9 @@ struct JoinerPlan {
   int grid;                 // workgroups (XCD-interleaved tile order)
   size_t lds;               // dynamic LDS bytes
 };
+
+// Compute units of the current device, 0 if unknown (cached per device).
+int device_cus();
 
 // topk: the joiner writes each row's best labels (trivial graph) instead of logits
 JoinerPlan plan_joiner(const ModelDev& m, int rows, int ncu, bool topk = false);

@@ -4049,9 +4049,9 @@ hipError_t launch_joiner_direct(const ModelDev& m, const JoinArgs& a, const Join
 template <bool BF16, bool TOPK, bool DENSE>
 hipError_t launch_joiner_sweep(const ModelDev& m, const JoinArgs& a, const JoinerPlan& p,
                                hipStream_t st) {
+  static LdsGrant grant;
   if (p.lds > 65536) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_joiner_sweep<BF16, TOPK, DENSE>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
+    const hipError_t e = grant((const void*)k_joiner_sweep<BF16, TOPK, DENSE>, p.lds);
     if (e != hipSuccess) return e;
   }
   launch_k((k_joiner_sweep<BF16, TOPK, DENSE>), dim3(p.grid), dim3(kSweepThreads), p.lds, st, m, a);
@@ -4360,8 +4360,7 @@ hipError_t launch_group_rg(int RG, const ModelDev& m, const GraphDev& g, const D
   }
 }
 
-// Compute units of the current device (cached per device).
-static int device_cus() {
+int device_cus() {
   static int cus[64] = {0};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;

@@ -560,13 +560,13 @@ struct RingPlan {
 // ring too large; chunks are as long as the workers' registers and the LDS allow (fewer
 // barriers).  More utterances than compute units: half the LDS, so that two workgroups
 // share one.
-RingPlan plan_ring(int kind, int B, int T, int U, bool alpha) {
+RingPlan plan_ring(int kind, int B, int T, int U, bool alpha, int ncu) {
   const RingPlan none{0, 0, 0, 0, 0};
   const int U1 = U + 1;
   if (T + U > kRingMaxSteps) return none;
   int K0 = 1;
   while (64 * K0 < U1) K0 *= 2;
-  for (int half = B > 256; half >= 0; --half)
+  for (int half = B > ncu; half >= 0; --half)
     for (int K = K0; K <= kTransducerMaxK; K *= 2) {
       const int cells = round_up(U1, K);
       // eq. (1): lane l reads row s - l, so the lanes' addresses step by K - rs cells: odd,
@@ -590,9 +590,9 @@ template <int K, int KIND, bool ALPHA>
 hipError_t launch_ring_t(const RingPlan& p, const float* blank, const float* label,
                          const int* lengths, int B, int T, int U, double* total, float* alpha,
                          int* status, hipStream_t st) {
+  static LdsGrant grant;
   if (p.lds > 65536) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_transducer_ring<K, KIND, ALPHA>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
+    const hipError_t e = grant((const void*)k_transducer_ring<K, KIND, ALPHA>, p.lds);
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((k_transducer_ring<K, KIND, ALPHA>), dim3(B), dim3(kRingThreads), p.lds, st, blank,
@@ -632,7 +632,7 @@ hipError_t launch_transducer_forward(int kind, const float* blank, const float* 
                                      float* alpha, int* status, hipStream_t st) {
   if (B == 0) return hipSuccess;
   if (U + 1 > 64 * kTransducerMaxK) return hipErrorInvalidValue;
-  const RingPlan p = plan_ring(kind, B, T, U, alpha != nullptr);
+  const RingPlan p = plan_ring(kind, B, T, U, alpha != nullptr, device_cus());
   if (kind == 0) return launch_kind<0>(p, blank, label, lengths, B, T, U, total, alpha, status, st);
   if (kind == 1) return launch_kind<1>(p, blank, label, lengths, B, T, U, total, alpha, status, st);
   return launch_kind<2>(p, blank, label, lengths, B, T, U, total, alpha, status, st);
