@@ -1384,7 +1384,8 @@ __global__ __launch_bounds__(128 * WN, MBW == 2 ? 3 : 1) void k_joiner(ModelDev 
 // block's h rows on their way to the other LDS buffer meanwhile.  Every h row is then read
 // once per 128 (256) columns and W once per workgroup, no operand is loaded twice by a
 // wave, and a logit's products go to several short accumulator chains (as in the small
-// tile, whose error it has; the GEMM tiles' single chain of 48 loses twice as much).
+// tile, whose error it has; the GEMM tiles' single chain of 48 loses twice as much, and two
+// chains instead of four for bf16 a sixth).
 // Bound: per block the LDS gives each wave its 2 KB (1 KB) of h per k-step, which takes as
 // long as the step's MFMAs.  Grid: column tiles x row groups, one workgroup per compute
 // unit; a group takes an equal, consecutive share of the batch's blocks.
@@ -1401,7 +1402,7 @@ constexpr int kSweepStride = kSweepK * (BF16 ? 2 : 4) + 16;  // LDS bytes per h 
 template <bool BF16, bool TOPK, bool DENSE>
 __global__ __launch_bounds__(kSweepThreads) void k_joiner_sweep(ModelDev m, JoinArgs a) {
   constexpr int NT = kSweepThreads, NB = BF16 ? 2 : 1;  // 16-column blocks per wave
-  constexpr int NC = BF16 ? 2 : 6;                      // accumulator chains per block
+  constexpr int NC = BF16 ? 4 : 6;                      // accumulator chains per block
   constexpr int STRIDE = kSweepStride<BF16>, BUF = 16 * STRIDE;
   constexpr int CPR = kSweepK * (BF16 ? 2 : 4) / 16;    // 16-byte chunks per h row
   constexpr int U = 16 * CPR / NT;                      // chunks per thread and block
@@ -1498,8 +1499,8 @@ __global__ __launch_bounds__(kSweepThreads) void k_joiner_sweep(ModelDev m, Join
         const uint4 h = *reinterpret_cast<const uint4*>(hb + 64 * s);
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
-          acc[nb][s & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(h), as_bf16x8(wb[nb][s]),
-                                                                   acc[nb][s & 1], 0, 0, 0);
+          acc[nb][s & 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(h), as_bf16x8(wb[nb][s]),
+                                                                   acc[nb][s & 3], 0, 0, 0);
       } else {
         const f16x8 ah = as_f16x8(*reinterpret_cast<const uint4*>(hb + 128 * s));
         const f16x8 al = as_f16x8(*reinterpret_cast<const uint4*>(hb + 128 * s + 16));
@@ -1520,7 +1521,7 @@ __global__ __launch_bounds__(kSweepThreads) void k_joiner_sweep(ModelDev m, Join
       for (int nb = 0; nb < NB; ++nb) {
         float zs;
         if constexpr (BF16)
-          zs = acc[nb][0][i] + acc[nb][1][i];
+          zs = (acc[nb][0][i] + acc[nb][1][i]) + (acc[nb][2][i] + acc[nb][3][i]);
         else
           zs = unsplit(acc[nb][0][i] + acc[nb][3][i],
                        (acc[nb][1][i] + acc[nb][2][i]) + (acc[nb][4][i] + acc[nb][5][i]), zscale);

@@ -206,3 +206,20 @@ def test_joiner_infinite_weight(V, C, R):
     assert (got[:, 3] == -np.inf).all()
     assert np.abs(got - want)[:, keep].max() <= (2e-7 * np.abs(want[:, keep]).max() +
                                                  2 * LOGIT_EPS * np.sqrt(C) * own)
+
+
+@pytest.mark.parametrize("V,C,R", [(500, 512, 512), (500, 512, 3000), (1000, 512, 300)])
+def test_joiner_bf16_sum_error(V, C, R):
+    """The sums over C of the bf16 sweep at large logits, where they set the error (the
+    median, so that the few tanh that round to a neighbouring bf16 value do not count).  With
+    16 products of 32 in chains of four the median is 7.8e-7 to 8.1e-7, in chains of eight,
+    whose partial sums are larger, 9.1e-7 to 9.4e-7."""
+    rng = np.random.default_rng(V + R)
+    m = synth.make_model(rng, V, C, 0.5)
+    enc = rng.standard_normal((R, C), dtype=np.float32)
+    a, b = rng.integers(0, V, R), rng.integers(0, V, R)
+    got = _logp_gpu(m, enc, a, b, dtype="bf16")
+    want = oracle.logp(m, enc, a.astype(np.int32), b.astype(np.int32), bf16=True)
+    med = np.median(np.abs(got - want))
+    say(f"  median |dlogp| = {med:.3g}")
+    assert med <= 8.6e-7
