@@ -1045,8 +1045,8 @@ constexpr float kLog2e = 1.44269504088896341f;
 // each wave 16 MBW rows x 64 columns (MBW x 4 MFMA blocks of 16 x 16):
 //  - 64 x 128 (MBW = 2, WN = 2; four waves, three workgroups per compute unit);
 //  - 256 x 256 (MBW = 8, WN = 4; eight waves), for bf16 batches with several such
-//    tiles per compute unit: half the operand bytes per product of a 128 x 128 tile, and
-//    a quarter fewer LDS fragment reads per MFMA.
+//    tiles per compute unit: a third of the operand bytes per product of the 64 x 128 tile,
+//    and half the LDS fragment reads per MFMA.
 // fp32 operands come as fp16 pairs (internal.h), three MFMAs per product: 16 times the
 // rate of the fp32 MFMA for three times the instructions, with a smaller error against
 // 64 bits than 512 fp32 additions (V = 5,000, 4,000 rows: 9e-8 of the log-probabilities
@@ -4120,7 +4120,7 @@ JoinerPlan plan_joiner(const ModelDev& m, int rows, int ncu, bool topk) {
   p.small = p.sweep = false;
   const int esz = bf16 ? 2 : 4;
   const int nvt = Vpad / kJoinerBN;
-  if (m.direct) {
+  if (m.direct) {  // fp32 products: internal.h
     p.small = true;
     p.n_rt = (rows + 15) / 16;
     p.n_ct = nvt;
@@ -4140,14 +4140,14 @@ JoinerPlan plan_joiner(const ModelDev& m, int rows, int ncu, bool topk) {
       return p;
     }
   }
-  // 64 x 128 GEMM tiles when there are at least two per compute unit (the count below is of
-  // 128 x 128): they read each operand less often than the sweep.  (Joiner alone, fp32,
+  // 64 x 128 GEMM tiles when there are at least two per compute unit (counted in pairs, one
+  // above the other): they read each operand less often than the sweep.  (Joiner alone, fp32,
   // C = 512, MI355X: V = 1,300, 2,048 rows 37.7 us against 41.3, 6,000 rows 77.7 against
   // 87.1.  They already lead by a little at one per compute unit, but their error, 9e-8,
   // is above the 7e-8 of the other two.)
-  p.n_rt = (rows + 127) / 128;
+  const int pairs = (rows + 2 * kJHalfBM - 1) / (2 * kJHalfBM);
   p.n_ct = (nvt + 1) / 2;
-  if ((long long)p.n_rt * p.n_ct >= ncu) {
+  if ((long long)pairs * p.n_ct >= ncu) {
     p.n_rt = (rows + kJHalfBM - 1) / kJHalfBM;
     p.lds = kJHalfLds;
     p.grid = joiner_grid(p.n_rt, p.n_ct);
@@ -4172,6 +4172,8 @@ JoinerPlan plan_joiner(const ModelDev& m, int rows, int ncu, bool topk) {
       return p;
     }
   }
+  // Small tiles otherwise; of 32 rows where they share W and leave a tile per compute unit
+  // (figures with the tile).
   p.small = true;
   if (bf16 && Kpad == 1024 && (long long)((rows + 31) / 32) * nvt >= ncu) {
     p.MB = 2;

@@ -218,8 +218,8 @@ def test_throughput_sampled(schedule):
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_trivial_wide_frame_joiner(dtype, B):
     # trivial graph on the frame schedule with enough joiner rows (B streams, 8 contexts)
-    # and columns (V = 2,000) for the GEMM tiles' top-label epilogue: B = 256 gives one
-    # 128 x 128 tile per CU (the 64 x 128 tiles run), B = 1,024 four (the 128 x 128 tiles)
+    # and columns (V = 2,000) for the 64 x 128 GEMM tiles' top-label epilogue: B = 256 gives
+    # two tiles per CU, the fewest that run them, B = 1,024 eight
     rng = np.random.default_rng(11)
     model = synth.make_model(rng, 2000, 256, 0.05)
     inputs = synth.make_inputs(rng, B, 6, 256, length_range=(0, 6))
