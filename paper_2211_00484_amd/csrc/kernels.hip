@@ -551,8 +551,7 @@ __global__ __launch_bounds__(256) void k_h_rows(ModelDev m, const float* __restr
                                                 const int* __restrict__ ctx, long long row0,
                                                 int per_enc, long long enc_stride, int R,
                                                 void* __restrict__ h) {
-  const int lane = threadIdx.x & 63, wave = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int wpr = m.Kpad / 512, r = wave / wpr, k0 = 512 * (wave - r * wpr);
+  const int lane = threadIdx.x & 63, r = blockIdx.x * 4 + (threadIdx.x >> 6), k0 = 512 * blockIdx.y;
   if (r >= R) return;  // whole wave
   const long long g = row0 + r;
   const int c = ctx[g], C = m.C, Kpad = m.Kpad;
@@ -585,8 +584,10 @@ __global__ __launch_bounds__(256) void k_h_rows(ModelDev m, const float* __restr
       *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(h) + o) =
           make_uint2((unsigned)f32_to_bf16_rne(h0) | ((unsigned)f32_to_bf16_rne(h1) << 16),
                      (unsigned)f32_to_bf16_rne(h2) | ((unsigned)f32_to_bf16_rne(h3) << 16));
+    } else if (m.direct) {
+      *reinterpret_cast<float4*>(reinterpret_cast<float*>(h) + o) = make_float4(h0, h1, h2, h3);
     } else {
-      *reinterpret_cast<uint4*>(reinterpret_cast<unsigned*>(h) + o) = h_quad(m.direct, h0, h1, h2, h3);
+      *reinterpret_cast<uint4*>(reinterpret_cast<unsigned*>(h) + o) = h_quad(0, h0, h1, h2, h3);
     }
   }
 }
@@ -4417,7 +4418,7 @@ hipError_t launch_h_rows_dense(const ModelDev& m, const float* enc, long long en
                                const int* ctx, long long row0, int per_enc, int R, void* h,
                                hipStream_t st) {
   if (R <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_h_rows, dim3((R * (m.Kpad / 512) + 3) / 4), dim3(256), 0, st, m, enc, ctx, row0, per_enc,
+  hipLaunchKernelGGL(k_h_rows, dim3((R + 3) / 4, m.Kpad / 512), dim3(256), 0, st, m, enc, ctx, row0, per_enc,
                      enc_stride, R, h);
   return hipGetLastError();
 }

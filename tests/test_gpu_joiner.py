@@ -13,7 +13,7 @@ SHAPES = [  # (V, C, sigma, R)
     (500, 512, 0.05, 70),     # Standard / Graph / Throughput shapes
     (5000, 512, 0.05, 20),    # Large shapes
     (129, 100, 0.3, 33),      # ragged V and C (padding paths)
-    # enough rows for the 64 x 128 GEMM tiles (two per compute unit) and, C = 100, the sweep:
+    # enough rows for the 64 x 128 GEMM tiles (two per compute unit):
     (5000, 512, 0.05, 2100),  # Large shapes, ragged row tile
     (129, 100, 0.3, 16500),   # odd number of 64-column tiles, ragged K and rows
 ]
