@@ -627,11 +627,10 @@ __device__ __forceinline__ int active_contexts(const JoinArgs& a, int b) {
 // The batch's active rows in (stream, context slot) order: rows b * Nc + j for the j <
 // nctx[b] contexts of each stream within its length.  Packing them leaves no tile of a
 // grid, which is sized for Nc rows per stream, with holes (a beam keeps about half of the
-// contexts it may).  Each thread takes consecutive streams; the counts of the first few
-// stay in registers (a second read would be one more round trip).
-template <int NT>
+// contexts it may).  Each thread takes consecutive streams; the counts of the first kHeld
+// are read together and stay in registers (every further one is a round trip of its own).
+template <int NT, int kHeld>
 struct PackedRows {
-  static constexpr int kHeld = 4;
   int b0, b1, pos, total;  // this thread's streams, the rows before them, all rows
   int held[kHeld];
   // Every thread calls it; s_wsum: [NT / 64].  One barrier (of LDS accesses only: loads
@@ -642,10 +641,12 @@ struct PackedRows {
     b0 = min(tid * per, a.B);
     b1 = min(b0 + per, a.B);
     int n = 0;
+    // (no branches around the loads, which would wait for one another)
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i) held[i] = active_contexts(a, min(b0 + i, a.B - 1));
 #pragma unroll
     for (int i = 0; i < kHeld; ++i) {
-      held[i] = 0;
-      if (b0 + i < b1) held[i] = active_contexts(a, b0 + i);
+      held[i] = b0 + i < b1 ? held[i] : 0;
       n += held[i];
     }
     for (int b = b0 + kHeld; b < b1; ++b) n += active_contexts(a, b);
@@ -679,10 +680,10 @@ struct PackedRows {
 // the last).  0: there are none; 2: they are rows r0 and on themselves (every row of the
 // batch is active), and s_row is to be read after the caller's next barrier only; else 1.
 // Every thread calls it.
-template <int NT, int BM>
-__device__ __forceinline__ int joiner_tile_rows(const JoinArgs& a, int r0, int* s_row, int* s_wsum) {
+template <int NT, int BM, int kHeld>
+__device__ __forceinline__ int pack_tile_rows(const JoinArgs& a, int r0, int* s_row, int* s_wsum) {
   const int tid = threadIdx.x;
-  PackedRows<NT> rows;
+  PackedRows<NT, kHeld> rows;
   rows.total = a.R;
   if (!a.rows_mode) {
     for (int i = tid; i < BM; i += NT) s_row[i] = -1;
@@ -696,6 +697,16 @@ __device__ __forceinline__ int joiner_tile_rows(const JoinArgs& a, int r0, int* 
   rows.write(a, r0, r0 + BM, s_row);
   lds_only_barrier();
   return 1;
+}
+// Streams per thread whose counts are held, by the batch.  (bf16, V = 5,000, every row
+// active: B = 8,192 with 4 held 1,400 us per frame, with 16 1,360, without packing 1,275, whose
+// early frames with few contexts take 1,020 for 390; B = 1,024 with 16 125, with 4 118,
+// without packing 134; B = 128 with 16 23.1, with 1 22.2.)
+template <int NT, int BM>
+__device__ __forceinline__ int joiner_tile_rows(const JoinArgs& a, int r0, int* s_row, int* s_wsum) {
+  if (a.rows_mode || a.B <= NT) return pack_tile_rows<NT, BM, 1>(a, r0, s_row, s_wsum);
+  if (a.B <= 4 * NT) return pack_tile_rows<NT, BM, 4>(a, r0, s_row, s_wsum);
+  return pack_tile_rows<NT, BM, 16>(a, r0, s_row, s_wsum);
 }
 
 // Tile of workgroup i, which runs on XCD i mod 8.  When the column tiles divide (nearly)
@@ -1447,7 +1458,7 @@ __global__ __launch_bounds__(kSweepThreads) void k_joiner_sweep(ModelDev m, Join
 
   // this group's rows: blocks [grp * q, (grp + 1) * q) of the active rows, q blocks each
   int total = a.R;
-  PackedRows<NT> rows;
+  PackedRows<NT, 4> rows;
   if (!DENSE) {
     rows.count(a, s_wsum);
     total = rows.total;

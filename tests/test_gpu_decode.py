@@ -227,6 +227,18 @@ def test_trivial_wide_frame_joiner(dtype, B):
          streams=range(0, B, B // 8), schedule="frame")
 
 
+@pytest.mark.parametrize("B,V", [(1500, 600), (4500, 600), (4500, 100)])
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_very_wide_batch_packed_rows(dtype, B, V):
+    # several streams per thread in the row packing of the 64 x 128 tiles (V = 600; 6, and 18
+    # of which 16 are held) and of the sweep (V = 100; 9, 4 held), ragged so that rows shift
+    rng = np.random.default_rng(B + V)
+    model = synth.make_model(rng, V, 100, 0.1)
+    inputs = synth.make_inputs(rng, B, 5, 100, length_range=(0, 5))
+    _run((inputs, model, synth.trivial_graph(V)), math.inf, 8, 8, dtype=dtype,
+         streams=list(range(0, B, B // 9)) + [B - 1], schedule="frame")
+
+
 def test_general_graph_wide_batch():
     # general graph on the frame schedule with B = 1,024 streams: four search workgroups
     # per CU over the batch, two of them resident on a CU at a time (each allocates the
