@@ -624,32 +624,30 @@ __device__ __forceinline__ int active_contexts(const JoinArgs& a, int b) {
   return a.t < len ? n : 0;
 }
 
-// The batch's active rows in (stream, context slot) order: rows b * Nc + j for the j <
+// The batch's active rows, in one order for all workgroups: rows b * Nc + j for the j <
 // nctx[b] contexts of each stream within its length.  Packing them leaves no tile of a
 // grid, which is sized for Nc rows per stream, with holes (a beam keeps about half of the
-// contexts it may).  Each thread takes consecutive streams; the counts of the first kHeld
-// are read together and stay in registers (every further one is a round trip of its own).
+// contexts it may).  Thread tid takes streams tid, tid + NT, ... (so that a wave's reads are
+// contiguous) and the rows go by thread; the counts of the first kHeld are read together and
+// stay in registers (every further one is a round trip of its own).
 template <int NT, int kHeld>
 struct PackedRows {
-  int b0, b1, pos, total;  // this thread's streams, the rows before them, all rows
+  int pos, total;  // the rows before this thread's, all rows
   int held[kHeld];
   // Every thread calls it; s_wsum: [NT / 64].  One barrier (of LDS accesses only: loads
   // requested before it stay in flight).
   __device__ __forceinline__ void count(const JoinArgs& a, int* s_wsum) {
     const int tid = threadIdx.x, wave = tid >> 6;
-    const int per = (a.B + NT - 1) / NT;
-    b0 = min(tid * per, a.B);
-    b1 = min(b0 + per, a.B);
     int n = 0;
     // (no branches around the loads, which would wait for one another)
 #pragma unroll
-    for (int i = 0; i < kHeld; ++i) held[i] = active_contexts(a, min(b0 + i, a.B - 1));
+    for (int i = 0; i < kHeld; ++i) held[i] = active_contexts(a, min(tid + i * NT, a.B - 1));
 #pragma unroll
     for (int i = 0; i < kHeld; ++i) {
-      held[i] = b0 + i < b1 ? held[i] : 0;
+      held[i] = tid + i * NT < a.B ? held[i] : 0;
       n += held[i];
     }
-    for (int b = b0 + kHeld; b < b1; ++b) n += active_contexts(a, b);
+    for (int b = tid + kHeld * NT; b < a.B; b += NT) n += active_contexts(a, b);
     const int incl = (int)wave_incl_scan_u32((unsigned)n);
     if ((tid & 63) == 63) s_wsum[wave] = incl;
     lds_only_barrier();
@@ -670,9 +668,10 @@ struct PackedRows {
       for (int j = max(0, r0 - p); j < nb && p + j < r1; ++j) list[p + j - r0] = b * a.Nc + j;
       p += nb;
     };
+    const int tid = threadIdx.x;
 #pragma unroll
-    for (int i = 0; i < kHeld; ++i) put(b0 + i, held[i]);
-    for (int b = b0 + kHeld; b < b1 && p < r1; ++b) put(b, active_contexts(a, b));
+    for (int i = 0; i < kHeld; ++i) put(tid + i * NT, held[i]);
+    for (int b = tid + kHeld * NT; b < a.B && p < r1; b += NT) put(b, active_contexts(a, b));
   }
 };
 
@@ -698,10 +697,10 @@ __device__ __forceinline__ int pack_tile_rows(const JoinArgs& a, int r0, int* s_
   lds_only_barrier();
   return 1;
 }
-// Streams per thread whose counts are held, by the batch.  (bf16, V = 5,000, every row
-// active: B = 8,192 with 4 held 1,400 us per frame, with 16 1,360, without packing 1,275, whose
-// early frames with few contexts take 1,020 for 390; B = 1,024 with 16 125, with 4 118,
-// without packing 134; B = 128 with 16 23.1, with 1 22.2.)
+// Streams per thread whose counts are held, by the batch.  (bf16, V = 5,000, B = 8,192: 1,160
+// us per frame with every row active and 140 with one context each; 1,360 and 390 with a
+// thread's streams consecutive, where each read touched a line per lane; 1,275 and 1,020
+// without packing.  B = 128: 16 held 23.1 us, one 22.2.)
 template <int NT, int BM>
 __device__ __forceinline__ int joiner_tile_rows(const JoinArgs& a, int r0, int* s_row, int* s_wsum) {
   if (a.rows_mode || a.B <= NT) return pack_tile_rows<NT, BM, 1>(a, r0, s_row, s_wsum);
@@ -1161,7 +1160,8 @@ __global__ __launch_bounds__(128 * WN, MBW == 2 ? 3 : 1) void k_joiner(ModelDev 
 #pragma unroll
   for (int u = 0; u < UA; ++u) {
     const int c = tid + NT * u;
-    const int r = rows == 2 ? min(r0 + (c >> 3), a.R - 1) : max(s_row[c >> 3], s_row[0]);
+    const int own = s_row[c >> 3];
+    const int r = rows == 2 ? min(r0 + (c >> 3), a.R - 1) : own >= 0 ? own : s_row[0];
     ha[u] = (unsigned)r * rowb32 + (c & 7) * 16;
   }
   // the epilogue's bias and scale values (clamped: past the vocabulary they are never used),
